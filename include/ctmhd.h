@@ -89,7 +89,8 @@ typedef struct ctmhd_params {
   int32_t flag_criteria; /* OR of CTMHD_FLAG_* */
   int32_t precision;     /* CTMHD_FP64, CTMHD_FP32 or CTMHD_FP32_R64 */
   int32_t tile;          /* launch-shape knob (0 = defaults): bits 0-7 minimum faces per
-                            marching chunk of the face pass (default 32), bits 8-15
+                            marching chunk of the face pass (0: by the size of the
+                            call, up to 32), bits 8-15
                             256-element strips per work item of the batched call (default 1),
                             bit 16 schedule of the batched call (0 one launch per phase,
                             1 one persistent launch per step), bits 19-20 XCD mapping of
@@ -98,8 +99,9 @@ typedef struct ctmhd_params {
                             XCD a contiguous range of tiles, 2 all XCDs on bands of one
                             plane), bits 21-22 Q26 edge kernel of ctmhd_step (0 automatic,
                             1 one thread per edge position, 2 one thread per column of
-                            edges marching along z; the same values), bits 24-30 x-face row
-                            segments per wavefront of the face pass (default 4); other
+                            edges marching along z; the same values), bits 24-30 runs of 64
+                            x-row cells per wavefront of the face pass (0: by the size
+                            of the call, up to 4); other
                             values are rejected with CTMHD_EARG */
   /* Test hook: NULL, or a DEVICE mask of 2 * n0*n1*n2 bytes (stage-1 mask then
    * stage-2 mask, interior cells, x0 fastest) OR-ed into the invalid-cell

@@ -1103,7 +1103,7 @@ int adjoint_box(const ctmhd_params* p_in, const ctmhd_box* box, const double* co
   State S0;
   for (int m = 0; m < 5; ++m) S0.c[m] = const_cast<double*>(cons_n[m]);
   for (int a = 0; a < 3; ++a) S0.b[a] = const_cast<double*>(bface_n[a]);
-  const FacePlan FP = make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p));
+  const FacePlan FP = box_face_plan(p, *box, G);
   const int ninter = G.n[0] * G.n[1] * G.n[2];
   const int nb = nblocks(G.elems);
   const UpdateCfg U = adj_update_cfg(p);
@@ -1144,7 +1144,7 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
   State user;
   for (int m = 0; m < 5; ++m) user.c[m] = cons[m];
   for (int a = 0; a < 3; ++a) user.b[a] = bface[a];
-  const FacePlan FP = make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p));
+  const FacePlan FP = box_face_plan(p, *box, G);
   const int ninter = G.n[0] * G.n[1] * G.n[2];
   const int nb = nblocks(G.elems);
   const UpdateCfg U = adj_update_cfg(p);

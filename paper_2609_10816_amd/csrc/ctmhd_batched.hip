@@ -91,6 +91,10 @@ long long item_count(int kind, const Geom& G, const FacePlan& FP, long long per,
   }
 }
 
+// Layout and meaning of a plan's contents: part of its key, so that a plan
+// kept from a library with another one is refused.
+constexpr int kPlanVersion = 2;
+
 // FNV-1a over everything a plan depends on: the kernel refuses a plan whose
 // key differs from the one computed for the call's own parameters and boxes.
 unsigned long long plan_key(const ctmhd_params* p, const ctmhd_box* boxes, int nbox,
@@ -100,8 +104,8 @@ unsigned long long plan_key(const ctmhd_params* p, const ctmhd_box* boxes, int n
     const unsigned char* c = (const unsigned char*)v;
     for (size_t i = 0; i < n; ++i) h = (h ^ c[i]) * 0x100000001b3ull;
   };
-  const int f[8] = {p->recon, p->emf_compute, p->fofc, tile_strips(p), tile_chunk(p),
-                   tile_xrows(p), nbox, L ? 1 : 0};
+  const int f[9] = {p->recon, p->emf_compute, p->fofc, tile_strips(p), tile_chunk(p),
+                   tile_xrows(p), nbox, L ? 1 : 0, kPlanVersion};
   mix(f, sizeof(f));
   if (L) {
     mix(L->domain, sizeof(L->domain));
@@ -370,15 +374,24 @@ int persistent_blocks(K kernel) {
   return ncu * per;
 }
 
+// Marched faces of all boxes of a call (the launch shape of the face pass).
+long long call_march_faces(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, bool level) {
+  long long f = 0;
+  for (int b = 0; b < nbox; ++b) f += march_faces(boxes[b], p->recon, p->emf_compute, !level);
+  return f;
+}
+
 // Items of every phase summed over the boxes (the grid of each phased launch;
 // the same counts as the plan's prefix sums).
 int phase_items(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, bool level,
                 const int* kind, int nphase, long long* items) {
   const long long per = (long long)kBlock * tile_strips(p);
+  const long long faces = call_march_faces(p, boxes, nbox, level);
   for (int q = 0; q < nphase; ++q) items[q] = 0;
   for (int b = 0; b < nbox; ++b) {
     const Geom G = make_geom(boxes[b]);
-    const FacePlan FP = make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p));
+    const FacePlan FP = make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p),
+                                       !level, faces, nbox);
     for (int q = 0; q < nphase; ++q) items[q] += item_count(kind[q], G, FP, per, level);
   }
   for (int q = 0; q < nphase; ++q)
@@ -583,11 +596,13 @@ int build_plan(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, const Le
   const int strips = P->strips;
   const long long per = (long long)kBlock * strips;
   long long flag_off = 0;
+  const long long faces = call_march_faces(p, boxes, nbox, L != nullptr);
   for (int b = 0; b < nbox; ++b) {
     const ctmhd_box& bx = boxes[b];
     BoxDesc& d = desc[b];
     d.G = make_geom(bx);
-    d.FP = make_face_plan(d.G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p));
+    d.FP = make_face_plan(d.G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p), !L, faces,
+                         nbox);
     d.off = bx.offset;
     d.flag_off = L ? bx.offset : flag_off;  // a level indexes flags by storage position
     flag_off += box_inter_ll(bx);

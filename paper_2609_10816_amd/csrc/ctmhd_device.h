@@ -404,14 +404,26 @@ __device__ __forceinline__ T joule_pair(const Geom& G, int a, const double lo[4]
 // ---------------------------------------------------------------------------
 // Face pass (Sec. 2.2, eqs. emf:alpha-pm, emf:q26-facevel).
 // ---------------------------------------------------------------------------
-// Face ranges of one stage.  Faces of direction a: s_a in [lo_a, lo_a +
-// nf_a), transverse coordinates in [tlo, tlo + tlen) on both axes.
+// Face ranges of one stage.  Faces of direction a are solved at s_a in
+// [lo_a, lo_a + nf_a), transverse coordinates in [tlo, tlo + tlen).
+// A box that is periodic on itself (per = 1) solves each face once, on its
+// interior range, and stores the values at every position of the ghost shell
+// that the edge and update passes read too: the transverse positions
+// [plo, phi], and the upper boundary face along the normal.  Solving those
+// copies instead costs (n+1)(n+2r+2)^2 / n^3 of the faces per direction (PPM,
+// Q26: 1.03 at 512^3, 1.45 at 32^3, 3.4 at 8^3).  A box of a level (per = 0)
+// solves the shell itself, from its neighbours' cells.  Measured per launch
+// (with the x rows end to end, below): FP64 512^3 16.77 -> 16.46 ms, 128^3
+// 277 -> 253 us; 2000 boxes of 8 to 64 cells per axis, FP32, 9.27 -> 7.37 ms.
 struct FacePlan {
   int lo[3], nf[3];   // along the face normal
   int tlo, tlen[3];   // transverse range start (same on every axis) and length per axis
+  int per, plo, phi[3];
   int ulo[3], ulen[3];  // faces read by the update (Joule flux only there)
-  // x part: one wavefront per (row, segment)
-  int xseg, xnseg, xwaves, xrows, xblocks;  // xwaves = items; xrows items per wavefront
+  // x part: the rows, each extended by its halo to xw = nf + 2r + 1 cells, laid
+  // end to end; an item is 64 consecutive cells of that line
+  int xw, xlen, xwaves, xrows, xblocks;  // xwaves = items; xrows items per wavefront
+  int xdx, xdy, xdz;  // step of one item (64 - 2r - 1 cells) in (cell, row y, row z)
   // y and z parts: lane blocks x chunks
   int chunk[3], nchunk[3], lanes[3], lblocks[3], blocks[3];
   int total_blocks;
@@ -440,11 +452,16 @@ __device__ __forceinline__ void face_local(const State& S, const Geom& G, int s,
   face_local_raw<T>(R, a, gamma, v);
 }
 
+// What the face pass stores per face: the flux (global momentum order), the
+// outer wave speeds and the face velocity.
+template <typename T>
+struct FaceOut {
+  T F[5], ap, am, us;
+};
+
 template <typename T, int RIEMANN>
-__device__ __forceinline__ int solve_and_store(const Work<T>& W, int s, int a, int stage,
-                                               const T qL[7], const T qR[7], double bn_d,
-                                               double gamma_d, T jflux) {
-  const int b = (a + 1) % 3, c = (a + 2) % 3;
+__device__ __forceinline__ int solve_face(int a, const T qL[7], const T qR[7], double bn_d,
+                                          double gamma_d, T jflux, FaceOut<T>& o) {
   // the solver's arithmetic type: T, or float64 for kHLLD64 / kLLF64
   using RT = typename std::conditional<(RIEMANN >= kHLLD64), double, T>::type;
   FState<RT> L{(RT)qL[0], (RT)qL[1], (RT)qL[2], (RT)qL[3], (RT)qL[4], (RT)qL[5], (RT)qL[6]};
@@ -464,17 +481,104 @@ __device__ __forceinline__ int solve_and_store(const Work<T>& W, int s, int a, i
 #pragma unroll
   for (int m = 0; m < 5; ++m) F[m] = (T)Fr[m];
   F[4] += jflux;  // Joule energy flux (zero outside the faces the update reads, or eta = 0)
-  // Streaming stores: no later access of this kernel reads them, and keeping
-  // them out of the L2 leaves it to the state rows the marches re-read.
-  __builtin_nontemporal_store(F[0], &W.F[stage][a][0][s]);
-  __builtin_nontemporal_store(F[1], &W.F[stage][a][1 + a][s]);
-  __builtin_nontemporal_store(F[2], &W.F[stage][a][1 + b][s]);
-  __builtin_nontemporal_store(F[3], &W.F[stage][a][1 + c][s]);
-  __builtin_nontemporal_store(F[4], &W.F[stage][a][4][s]);
-  __builtin_nontemporal_store(ap, &W.ap[a][s]);
-  __builtin_nontemporal_store(am, &W.am[a][s]);
-  __builtin_nontemporal_store((ap * (T)L.un + am * (T)R.un) * trcp(ap + am), &W.us[a][s]);
+  o.F[0] = F[0];
+  o.F[1 + a] = F[1];
+  o.F[1 + (a + 1) % 3] = F[2];
+  o.F[1 + (a + 2) % 3] = F[3];
+  o.F[4] = F[4];
+  o.ap = ap;
+  o.am = am;
+  o.us = (ap * (T)L.un + am * (T)R.un) * trcp(ap + am);
   return fb;
+}
+
+// Streaming stores: no later access of this kernel reads them, and keeping
+// them out of the L2 leaves it to the state rows the marches re-read.
+template <typename T>
+__device__ __forceinline__ void store_flux(const Work<T>& W, int s, int a, int stage,
+                                           const FaceOut<T>& o) {
+#pragma unroll
+  for (int m = 0; m < 5; ++m) __builtin_nontemporal_store(o.F[m], &W.F[stage][a][m][s]);
+}
+template <typename T>
+__device__ __forceinline__ void store_speeds(const Work<T>& W, int s, int a, const FaceOut<T>& o) {
+  __builtin_nontemporal_store(o.ap, &W.ap[a][s]);
+  __builtin_nontemporal_store(o.am, &W.am[a][s]);
+  __builtin_nontemporal_store(o.us, &W.us[a][s]);
+}
+
+// Periodic copies p + m n_d, m in [mlo, mhi], of coordinate p of a solved x_a
+// face that the later passes read.
+__device__ __forceinline__ void image_range(const FacePlan& FP, const Geom& G, int a, int d, int p,
+                                            int& mlo, int& mhi) {
+  const int n = G.n[d];
+  mlo = 0;
+  mhi = 0;
+  if (d == a) {
+    mhi = p == FP.lo[a] ? 1 : 0;  // the upper boundary face
+  } else {
+    mlo = -((p - FP.plo) / n);
+    mhi = (FP.phi[d] - p) / n;
+  }
+}
+
+// Whether a transverse coordinate p has periodic copies in the shell.
+__device__ __forceinline__ bool has_image(const FacePlan& FP, const Geom& G, int d, int p) {
+  return FP.per && (p - G.n[d] >= FP.plo || p + G.n[d] <= FP.phi[d]);
+}
+
+// The copies of a solved face (per = 1): the flux at the upper boundary face
+// (the update reads it on interior rows only), alpha and u* at the positions
+// the edges read, which lie outside the interior along one transverse axis at
+// most.  Few faces get here: those within r + 1 of the box's sides.
+template <typename T>
+__device__ __forceinline__ void store_images(const Work<T>& W, const Geom& G, const FacePlan& FP,
+                                             const int s3[3], int s, int a, int stage,
+                                             const FaceOut<T>& o) {
+  const int b = (a + 1) % 3, c = (a + 2) % 3;
+  int la, ha, lb, hb, lc, hc;
+  image_range(FP, G, a, a, s3[a], la, ha);
+  image_range(FP, G, a, b, s3[b], lb, hb);
+  image_range(FP, G, a, c, s3[c], lc, hc);
+  for (int ma = la; ma <= ha; ++ma) {
+    const int sa = s + ma * G.n[a] * G.st[a];
+    if (ma) store_flux(W, sa, a, stage, o);
+    for (int mb = lb; mb <= hb; ++mb)
+      if (mb || ma) store_speeds(W, sa + mb * G.n[b] * G.st[b], a, o);
+    for (int mc = lc; mc <= hc; ++mc)
+      if (mc) store_speeds(W, sa + mc * G.n[c] * G.st[c], a, o);
+  }
+}
+
+// Positions a solved face stands for: the fallback counter counts every
+// position of the shell as one solved face.
+__device__ __forceinline__ int face_copies(const FacePlan& FP, const Geom& G, const int s3[3],
+                                           int a) {
+  int w = 1;
+  if (FP.per) {
+#pragma unroll
+    for (int d = 0; d < 3; ++d) {
+      int lo, hi;
+      image_range(FP, G, a, d, s3[d], lo, hi);
+      w *= hi - lo + 1;
+    }
+  }
+  return w;
+}
+
+// Solve the x_a face at s3 (storage index s) and store it; img: the face's
+// transverse coordinates have periodic copies.
+template <typename T, int RIEMANN>
+__device__ __forceinline__ int face_item(const Work<T>& W, const Geom& G, const FacePlan& FP,
+                                         const int s3[3], int s, int a, int stage, bool img,
+                                         const T qL[7], const T qR[7], double bn, double gamma,
+                                         T jflux) {
+  FaceOut<T> o;
+  const int fb = solve_face<T, RIEMANN>(a, qL, qR, bn, gamma, jflux, o);
+  store_flux(W, s, a, stage, o);
+  store_speeds(W, s, a, o);
+  if (img || (FP.per && s3[a] == FP.lo[a])) store_images(W, G, FP, s3, s, a, stage, o);
+  return fb ? face_copies(FP, G, s3, a) : 0;
 }
 
 // Whether the face pass's x_a face at s3 is one the update reads: [g, g+n]
@@ -554,49 +658,79 @@ __device__ __forceinline__ void recon_lanes(T q, T& qm, T& qp) {
   }
 }
 
+// The rows of the x part, each with its halo of r + 1 cells below and r above
+// the faces, are laid end to end, and item i holds cells [i (63 - 2r), ... + 63]
+// of that line, so that a wavefront wastes lanes on halos only: 89% of them
+// resolve faces at n = 128 (67% with three whole segments per row), 57% at
+// n = 8 (13%).
 template <typename T, int RECON, int RIEMANN>
 __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const FacePlan& FP,
                         int wave, int stage, double gamma, double eta, int& nfb) {
   constexpr int r = recon_halfwidth(RECON);
   const int lane = threadIdx.x & 63;
-  // this wavefront takes items [it, end) (item = row * xnseg + segment) and
-  // loads the cells of the next item before it resolves the current one
+  // this wavefront takes items [it, end) and loads the cells of the next item
+  // before it resolves the current one
   int it = wave * FP.xrows;
   const int end = it + FP.xrows < FP.xwaves ? it + FP.xrows : FP.xwaves;
-  auto locate = [&](int item, int& x, int& y, int& z) {
-    const int row = item / FP.xnseg, seg = item % FP.xnseg;
-    y = FP.tlo + row % FP.tlen[1];
-    z = FP.tlo + row / FP.tlen[1];
-    x = FP.lo[0] - (r + 1) + seg * FP.xseg + lane;
-    const int xc = x < 0 ? 0 : (x > G.N[0] - 2 ? G.N[0] - 2 : x);  // loads stay in the box
-    return xc + G.st[1] * y + G.st[2] * z;
+  // lane's cell: position x of extended row (y, z), all counted from the
+  // start of their ranges; lanes past the end of the line stay on its last row
+  int x, y, z;
+  {
+    const int e = it * (63 - 2 * r) + lane;
+    const int row = e / FP.xw;
+    x = e - row * FP.xw;
+    z = row / FP.tlen[1];
+    y = row - z * FP.tlen[1];
+  }
+  auto locate = [&](int s3[3]) {
+    const bool in = z < FP.tlen[2];
+    s3[0] = FP.lo[0] - (r + 1) + x;
+    s3[1] = FP.tlo + (in ? y : FP.tlen[1] - 1);
+    s3[2] = FP.tlo + (in ? z : FP.tlen[2] - 1);
+    return s3[0] + G.st[1] * s3[1] + G.st[2] * s3[2];
+  };
+  // whether this lane resolves a face: it holds a face position and its
+  // stencil lies in the wavefront
+  auto is_face = [&]() {
+    return lane >= r + 1 && lane <= 63 - r && x >= r + 1 && x <= r + FP.nf[0] && z < FP.tlen[2];
   };
   // whether this lane's face of an item needs the Joule flux; if so its
   // normal-field neighbours are loaded with the item's cell
-  auto joule_nb = [&](int x, int y, int z, int s, double nb[4]) {
-    const int s3[3] = {x, y, z};
-    const bool j = eta > 0.0 && lane >= r + 1 && lane <= 63 - r && x >= FP.lo[0] &&
-                   x < FP.lo[0] + FP.nf[0] && face_in_update(FP, s3, 0);
+  auto joule_nb = [&](const int s3[3], int s, double nb[4]) {
+    const bool j = eta > 0.0 && is_face() && face_in_update(FP, s3, 0);
     if (j) face_nb(S, G, s, 0, nb);
     return j;
   };
-  int xn, yn, zn;
-  int sn = locate(it, xn, yn, zn);
+  int n3[3];
+  int sn = locate(n3);
   CellRaw nxt;
   cell_load(S, G, sn, nxt);
   double nb_nxt[4] = {0.0, 0.0, 0.0, 0.0};
-  bool j_nxt = joule_nb(xn, yn, zn, sn, nb_nxt);
-  for (; it < end; ++it) {  // wavefront-uniform trip count (cross-lane shuffles below)
+  bool j_nxt = joule_nb(n3, sn, nb_nxt);
+  for (; it < end; ++it) {  // wavefront-uniform trip count (cross-lane shifts below)
     const CellRaw cur = nxt;
-    const int x = xn, s = sn;
+    const int s3[3] = {n3[0], n3[1], n3[2]};
+    const int s = sn;
     double nb[4];
 #pragma unroll
     for (int k = 0; k < 4; ++k) nb[k] = nb_nxt[k];
-    const bool jf_need = j_nxt;
+    const bool jf_need = j_nxt, face = is_face();
     if (it + 1 < end) {
-      sn = locate(it + 1, xn, yn, zn);
+      // the next item's cell: one item step, with carries into y and z
+      x += FP.xdx;
+      y += FP.xdy;
+      z += FP.xdz;
+      if (x >= FP.xw) {
+        x -= FP.xw;
+        ++y;
+      }
+      if (y >= FP.tlen[1]) {
+        y -= FP.tlen[1];
+        ++z;
+      }
+      sn = locate(n3);
       cell_load(S, G, sn, nxt);
-      j_nxt = joule_nb(xn, yn, zn, sn, nb_nxt);
+      j_nxt = joule_nb(n3, sn, nb_nxt);
     }
     T v[7];
     face_local_raw<T>(cur, 0, gamma, v);
@@ -611,10 +745,10 @@ __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const F
     cell_tfaces(cur, 0, thi);
 #pragma unroll
     for (int k = 0; k < 4; ++k) tlo[k] = lane_prev(thi[k]);
-    const bool face = lane >= r + 1 && lane <= 63 - r && x >= FP.lo[0] && x < FP.lo[0] + FP.nf[0];
     if (face) {
       const T jf = jf_need ? joule_pair<T>(G, 0, tlo, thi, cur.bl[0], nb, (T)eta) : T(0);
-      nfb += solve_and_store<T, RIEMANN>(W, s, 0, stage, qL, qm, cur.bl[0], gamma, jf);
+      const bool img = has_image(FP, G, 1, s3[1]) || has_image(FP, G, 2, s3[2]);
+      nfb += face_item<T, RIEMANN>(W, G, FP, s3, s, 0, stage, img, qL, qm, cur.bl[0], gamma, jf);
     }
   }
 }
@@ -638,6 +772,7 @@ __device__ void faces_march(const State& S, const Geom& G, const Work<T>& W, con
   if (f1 > FP.lo[A] + FP.nf[A]) f1 = FP.lo[A] + FP.nf[A];
   const int sa = G.st[A];
   const int base = s3[0] + G.st[C] * s3[C];
+  const bool img = has_image(FP, G, 0, s3[0]) || has_image(FP, G, C, s3[C]);
   ReconStream<RECON, T> rs[7];
   T qprev[7];
   // cells f0-1-r .. f1-1+r; the pushes before cell f0-1+r only warm up the
@@ -689,8 +824,9 @@ __device__ void faces_march(const State& S, const Geom& G, const Work<T>& W, con
 #pragma unroll
     for (int k = 0; k < 7; ++k) rs[k].push(v[k], qm[k], qp[k]);
     if (cell >= f0) {
-      const int s = base + cell * sa;
-      nfb += solve_and_store<T, RIEMANN>(W, s, A, stage, qprev, qm, bn, gamma, jd[r]);
+      s3[A] = cell;
+      nfb += face_item<T, RIEMANN>(W, G, FP, s3, base + cell * sa, A, stage, img, qprev, qm, bn,
+                                   gamma, jd[r]);
     }
 #pragma unroll
     for (int k = 0; k < 7; ++k) qprev[k] = qp[k];

@@ -28,13 +28,12 @@ int fail(int code, const char* msg) {
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 // Tuning knobs in ctmhd_params.tile: bits 0-7 minimum faces per marching
-// chunk (default 32), bits 8-15 256-element strips per batched work item
-// (default 1), bit 16 batched schedule (0 per phase, 1 persistent), bits
-// 19-20 XCD mapping, bits 21-22 Q26 edge kernel, bits 24-30 x-face row
-// segments per wavefront (default 4).
+// chunk (0: automatic, up to 32), bits 8-15 256-element strips per batched
+// work item (default 1), bit 16 batched schedule (0 per phase, 1 persistent),
+// bits 19-20 XCD mapping, bits 21-22 Q26 edge kernel, bits 24-30 x-face items
+// per wavefront (0: automatic, up to 4).
 int tile_chunk(const ctmhd_params* p) {
-  int c = p->tile & 0xff;
-  return c > 0 ? c : 32;
+  return p->tile & 0xff;
 }
 int tile_strips(const ctmhd_params* p) {
   int s = (p->tile >> 8) & 0xff;
@@ -65,11 +64,8 @@ int xcd_band(const ctmhd_params* p, long long plane_positions, long long total_p
   return band < 1 ? 1 : (int)band;
 }
 
-// bits 24-30: x-face items (row segments) per wavefront (default 4)
-int tile_xrows(const ctmhd_params* p) {
-  int x = (p->tile >> 24) & 0x7f;
-  return x > 0 ? x : 4;
-}
+// bits 24-30: x-face items (runs of 64 cells) per wavefront (0: automatic)
+int tile_xrows(const ctmhd_params* p) { return (p->tile >> 24) & 0x7f; }
 
 int check_params(const ctmhd_params* p) {
   if (!p) return fail(CTMHD_EARG, "params is NULL");
@@ -203,27 +199,69 @@ inline void prof_end(hipStream_t st) {
     if (hipGetLastError() != hipSuccess) return fail(CTMHD_EHIP, "kernel launch failed: " #kern); \
   } while (0)
 
-// Face plan: ranges and launch shape of the fused face kernel.
-FacePlan make_face_plan(const Geom& G, int recon, int emf, int chunk_min, int xrows) {
+// Launch shape of the face pass when the tile knob leaves it open, from the
+// faces of the two marching directions of all boxes of a call: chunks of 32
+// faces (16 in a call of many boxes, whose marches are of uneven length) once
+// they make kFaceWaves wavefronts, shorter ones on smaller calls, down to one
+// face.  A chunk is a serial chain of one Riemann solve (about 2 us) per face
+// and 2r + 1 cheaper cells to fill its pipeline.  Measured per step, FP64 PPM:
+// 16^3 94 us with chunks of 1, 112 with 4, 183 with 32; 64^3 267 / 220 / 216 /
+// 241 / 329 us with 1 / 4 / 8 / 16 / 32; 128^3 1259 / 1194 / 1165 / 1155 us
+// with 4 / 8 / 16 / 32; 100 uneven boxes 2657 / 2681 / 2790 us with 8 / 16 / 32.
+constexpr int kFaceWaves = 1024;
+int auto_face_chunk(long long faces, int nbox) {
+  const long long c = faces / (64LL * kFaceWaves), most = nbox > 1 ? 16 : 32;
+  return c < 1 ? 1 : (c > most ? (int)most : (int)c);
+}
+// Items per wavefront of the x part, one to four: 16^3 108 us with 4 against
+// 94 with 1, 64^3 230 against 216; 128^3 1153 against 1172.
+int auto_face_xrows(long long faces) {
+  const long long x = faces / (4 * 64LL * kFaceWaves);
+  return x < 1 ? 1 : (x > 4 ? 4 : (int)x);
+}
+
+// Faces of the two marching directions of one box.
+long long march_faces(const ctmhd_box& b, int recon, int emf, bool periodic) {
+  const int s = emf == CTMHD_EMF_Q26 ? recon_halfwidth(recon) : 0;
+  const long long t = periodic ? 0 : 2 + 2 * s, e = periodic ? 0 : 1;
+  return (b.n[0] + t) * ((b.n[1] + e) * (b.n[2] + t) + (b.n[2] + e) * (b.n[1] + t));
+}
+
+// Face plan: ranges and launch shape of the fused face kernel.  chunk_min and
+// xrows: the tile knob's values, 0 automatic from `faces` (march_faces summed
+// over the nbox boxes of the call).
+FacePlan make_face_plan(const Geom& G, int recon, int emf, int chunk_min, int xrows, bool periodic,
+                        long long faces, int nbox) {
+  if (chunk_min <= 0) chunk_min = auto_face_chunk(faces, nbox);
+  if (xrows <= 0) xrows = auto_face_xrows(faces);
   FacePlan P;
   const int r = recon_halfwidth(recon);
   const int g = G.g;
   // Q26 reconstructs u* along the transverse axes to the edges, which needs
   // faces r+1 beyond the edge range [g, g+n]; the other schemes only need
   // alpha on the faces next to the edges.
-  const int tlo = emf == CTMHD_EMF_Q26 ? g - 1 - r : g - 1;
-  P.tlo = tlo;
+  const int shell = emf == CTMHD_EMF_Q26 ? r : 0;
+  P.per = periodic ? 1 : 0;
+  P.plo = g - 1 - shell;
+  P.tlo = periodic ? g : P.plo;
   for (int d = 0; d < 3; ++d) {
+    P.phi[d] = g + G.n[d] + shell;
     P.lo[d] = g;
-    P.nf[d] = G.n[d] + 1;  // faces g .. g+n read by the update and the edges
-    P.tlen[d] = (emf == CTMHD_EMF_Q26 ? g + G.n[d] + r : g + G.n[d]) - tlo + 1;
+    // faces g .. g+n are read by the update and the edges; face g+n of a
+    // periodic box is a copy of face g
+    P.nf[d] = G.n[d] + (periodic ? 0 : 1);
+    P.tlen[d] = periodic ? G.n[d] : P.phi[d] - P.plo + 1;
     P.ulo[d] = g;
     P.ulen[d] = G.n[d];
   }
   // x part
-  P.xseg = 64 - 2 * r - 1;
-  P.xnseg = (P.nf[0] + P.xseg - 1) / P.xseg;
-  P.xwaves = P.xnseg * P.tlen[1] * P.tlen[2];
+  const int xstep = 64 - 2 * r - 1;
+  P.xw = P.nf[0] + 2 * r + 1;
+  P.xlen = P.xw * P.tlen[1] * P.tlen[2];
+  P.xwaves = (P.xlen - 2 * r - 1 + xstep - 1) / xstep;
+  P.xdx = xstep % P.xw;
+  P.xdy = xstep / P.xw % P.tlen[1];
+  P.xdz = xstep / P.xw / P.tlen[1];
   P.xrows = xrows;
   const int xwf = (P.xwaves + xrows - 1) / xrows;  // wavefronts of the x part
   P.xblocks = (xwf + kBlock / 64 - 1) / (kBlock / 64);
@@ -244,6 +282,12 @@ FacePlan make_face_plan(const Geom& G, int recon, int emf, int chunk_min, int xr
   }
   P.chunk[0] = P.nchunk[0] = P.lanes[0] = P.lblocks[0] = P.blocks[0] = 0;
   return P;
+}
+
+// The face plan of a single periodic box.
+FacePlan box_face_plan(const ctmhd_params* p, const ctmhd_box& b, const Geom& G) {
+  return make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p), true,
+                        march_faces(b, p->recon, p->emf_compute, true), 1);
 }
 
 template <typename T, int RECON>

@@ -141,8 +141,8 @@ def make_tile(chunk=0, strips=0, persistent=False, xrows=0, xcd_map="auto", emf_
     passes ("auto", "contiguous": each XCD a contiguous range of tiles,
     "banded": all XCDs on bands of the same plane), the single-box Q26 edge
     kernel ("auto", "edge": one thread per edge position, "march": one thread
-    per column of edges marching along z) and the x-face row segments per
-    wavefront (0: defaults)."""
+    per column of edges marching along z) and the runs of 64 x-row cells per
+    wavefront (0: chosen by the library from the size of the call)."""
     return ((int(chunk) & 0xFF) | ((int(strips) & 0xFF) << 8) | ((1 if persistent else 0) << 16)
             | (XCD_MAP[xcd_map] << 19) | (EMF_KERNEL[emf_kernel] << 21)
             | ((int(xrows) & 0x7F) << 24))
