@@ -2,6 +2,8 @@
 //
 // One RK2-SSP step with first-order flux correction (Sec. 2.5 of Kriel et al.)
 // is a short sequence of stream-ordered kernels on a ghosted box:
+//   k_start      once per call: ghost fill, CFL maximum and, for an odd number
+//                of steps, the copy into the other buffer
 //   k_dt_final   dt from the CFL maximum of the step's starting state (or the
 //                caller's dt); a non-finite dt stops the call
 //   per stage:
@@ -30,14 +32,6 @@ int g_prof_pairs = 0;
 int g_prof_used = 0;
 
 namespace {
-
-// Workgroups of the first-order and fix-up launches, which stride over the
-// box: enough to fill the chip when cells are flagged, few enough that the
-// usual launch with nothing flagged costs microseconds.
-inline int fix_blocks(int ninter) {
-  const int nb = nblocks(ninter);
-  return nb < 2048 ? nb : 2048;
-}
 
 template <typename T>
 int launch_fo(hipStream_t st, const ctmhd_params* p, State Sn, const Geom& G, const Work<T>& W,
@@ -78,12 +72,11 @@ int run_stage(hipStream_t st, const ctmhd_params* p, const Geom& G, const Work<T
   U.force = p->force_flags ? p->force_flags + (size_t)stage * ninter : nullptr;
   U.flag_storage = 0;
   const int band = xcd_band(p, (long long)G.n[0] * G.n[1], ninter);
-  LAUNCH(k_update<T>, nblocks(ninter), base, in, out, G, W, stage, 0, U, diag, band, W.stop);
-  if (p->fofc) {
-    if ((rc = launch_fo<T>(st, p, base, G, W, stage, ninter))) return rc;
-    LAUNCH(k_update<T>, fix_blocks(ninter), base, in, out, G, W, stage, 1, U, diag, band, W.stop);
-  }
-  return CTMHD_OK;
+  if ((rc = launch_update<T, 0>(st, nblocks(ninter), base, in, out, G, W, stage, U, diag, band)))
+    return rc;
+  if (!p->fofc) return CTMHD_OK;
+  if ((rc = launch_fo<T>(st, p, base, G, W, stage, ninter))) return rc;
+  return launch_update<T, 1>(st, fix_blocks(ninter), base, in, out, G, W, stage, U, diag, band);
 }
 
 template <typename T, int RECON>
@@ -95,33 +88,33 @@ int step_box(const ctmhd_params* p, const ctmhd_box* box, double* const cons[5],
   State B, H;
   int rc = build_work<T>(p, ws, ws_bytes, *box, W, B, H);
   if (rc) return rc;
-  State A;
-  for (int m = 0; m < 5; ++m) A.c[m] = cons[m];
-  for (int a = 0; a < 3; ++a) A.b[a] = bface[a];
-  const State user = A;
+  State user;
+  for (int m = 0; m < 5; ++m) user.c[m] = cons[m];
+  for (int a = 0; a < 3; ++a) user.b[a] = bface[a];
   const FacePlan FP = box_face_plan(p, *box, G);
   double dxmin = fmin(G.dx[0], fmin(G.dx[1], G.dx[2]));
   double sres = p->eta > 0.0 ? 2.0 * p->eta / (dxmin * dxmin) : 0.0;
-  const int ninter = G.n[0] * G.n[1] * G.n[2];
-  LAUNCH(k_init, 1, W.stop, W.smax, W.nflag);
-  LAUNCH(k_wrap, nblocks(G.elems), A, G, W.stop);
-  int dtb = nblocks(ninter);
-  if (dtb > 2048) dtb = 2048;
-  LAUNCH(k_dt, dtb, A, G, p->gamma, sres, W.smax, W.stop);
+  // steps alternate between the caller's buffers and B; an odd number of them
+  // starts from a copy in B, so that the last one ends in the caller's
+  const bool odd = nsteps & 1;
+  State A = odd ? B : user;
+  if (odd) B = user;
+  const State other = odd ? A : B;
+  int npart = 0;
+  if ((rc = launch_start(st, p, user, A, odd, G, W, dt_fixed == nullptr, sres, npart))) return rc;
   for (int n = 0; n < nsteps; ++n) {
     long long* dg = diag ? (long long*)diag + 4 * n : nullptr;
-    LAUNCH(k_dt_final, 1, W.smax, W.nflag, p->cfl, dt_fixed ? dt_fixed + n : nullptr, W.dt,
-           dt_out ? dt_out + n : nullptr, W.stop, dg);
+    LAUNCH(k_dt_final, 1, W.smax, start_part(W), npart, n, W.nflag, p->cfl,
+           dt_fixed ? dt_fixed + n : nullptr, W.dt, dt_out ? dt_out + n : nullptr, W.stop, dg);
     if ((rc = run_stage<T, RECON>(st, p, G, W, FP, A, A, H, 0, sres, dg))) return rc;
     if ((rc = run_stage<T, RECON>(st, p, G, W, FP, H, A, B, 1, sres, dg))) return rc;
-    // a stopped step leaves the state where it was: carry it to the next buffer
-    // (a capped grid: the launch almost always finds nothing to do)
-    LAUNCH(k_copy, fix_blocks(G.elems), B, A, G.elems, W.stop);
     State tmp = A;
     A = B;
     B = tmp;
   }
-  if (A.c[0] != user.c[0]) LAUNCH(k_copy, nblocks(G.elems), user, A, G.elems, (const int*)nullptr);
+  // a stopped call may have left its state in the other buffer (a capped grid:
+  // the launch almost always finds nothing to do)
+  LAUNCH(k_restore, fix_blocks(G.elems), user, other, G.elems, nsteps, W.stop);
   return CTMHD_OK;
 }
 

@@ -1099,7 +1099,6 @@ int adjoint_box(const ctmhd_params* p_in, const ctmhd_box* box, const double* co
     return adj_reverse<RECON, RIEMANN, EMF>(st, p, G, C, with_face_arrays(W, T, 1),
                                             with_face_arrays(C.W0, T, 0), T.S0, T.S1, Gin, Gout);
   }
-  LAUNCH(k_init, 1, W.stop, W.smax, W.nflag);
   State S0;
   for (int m = 0; m < 5; ++m) S0.c[m] = const_cast<double*>(cons_n[m]);
   for (int a = 0; a < 3; ++a) S0.b[a] = const_cast<double*>(bface_n[a]);
@@ -1109,17 +1108,18 @@ int adjoint_box(const ctmhd_params* p_in, const ctmhd_box* box, const double* co
   const UpdateCfg U = adj_update_cfg(p);
   State A = C.A, H = C.H;
   // forward: S0 with ghosts, the caller's dt, stage 1 into H = S1
-  LAUNCH(k_copy, nb, A, S0, G.elems, (const int*)nullptr);
-  LAUNCH(k_wrap, nb, A, G, W.stop);
-  LAUNCH(k_dt_final, 1, W.smax, W.nflag, p->cfl, dt, W.dt, (double*)nullptr, W.stop,
-         (long long*)nullptr);
+  int npart = 0;
+  if ((rc = launch_start(st, p, S0, A, true, G, W, false, 0.0, npart))) return rc;
+  LAUNCH(k_dt_final, 1, W.smax, start_part(W), 0, 0, W.nflag, p->cfl, dt, W.dt, (double*)nullptr,
+         W.stop, (long long*)nullptr);
   if ((rc = launch_faces<double, RECON>(st, p, A, G, W, FP, 0, nullptr))) return rc;
   LAUNCH(k_adj_save9, nb, G, W, C.W0);
   if constexpr (EMF != kQ26) LAUNCH((k_prim<double, EMF>), nb, A, G, W, p->gamma, W.stop);
   if constexpr (first_step_stored(EMF, RECON))
     LAUNCH((k_first_step<double, RECON, EMF>), nb, G, W, W.stop);
   if ((rc = launch_emf<double, RECON>(st, p, A, G, W, 0))) return rc;
-  LAUNCH(k_update<double>, nblocks(ninter), A, A, H, G, W, 0, 0, U, (long long*)nullptr, 0, W.stop);
+  if ((rc = launch_update<double, 0>(st, nblocks(ninter), A, A, H, G, W, 0, U, nullptr, 0)))
+    return rc;
   if ((rc = launch_faces<double, RECON>(st, p, H, G, W, FP, 1, nullptr))) return rc;
   return adj_reverse<RECON, RIEMANN, EMF>(st, p, G, C, W, C.W0, A, H, Gin, Gout);
 }
@@ -1149,17 +1149,14 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
   const int nb = nblocks(G.elems);
   const UpdateCfg U = adj_update_cfg(p);
   const Work<double> W0 = with_face_arrays(W, T, 0), W1 = with_face_arrays(W, T, 1);
-  LAUNCH(k_init, 1, W.stop, W.smax, W.nflag);
-  LAUNCH(k_copy, nb, T.S0, user, G.elems, (const int*)nullptr);
-  LAUNCH(k_wrap, nb, T.S0, G, W.stop);
-  if (!dt) {  // the CFL dt of S^n, as ctmhd_step computes it
-    const double dxmin = fmin(G.dx[0], fmin(G.dx[1], G.dx[2]));
-    const double sres = p->eta > 0.0 ? 2.0 * p->eta / (dxmin * dxmin) : 0.0;
-    int dtb = nblocks(ninter);
-    if (dtb > 2048) dtb = 2048;
-    LAUNCH(k_dt, dtb, T.S0, G, p->gamma, sres, W.smax, W.stop);
-  }
-  LAUNCH(k_dt_final, 1, W.smax, W.nflag, p->cfl, dt, W.dt, T.dt, W.stop, (long long*)nullptr);
+  // S^n with its ghosts and, without a given dt, its CFL dt, as ctmhd_step
+  // computes it
+  const double dxmin = fmin(G.dx[0], fmin(G.dx[1], G.dx[2]));
+  const double sres = p->eta > 0.0 ? 2.0 * p->eta / (dxmin * dxmin) : 0.0;
+  int npart = 0;
+  if ((rc = launch_start(st, p, user, T.S0, true, G, W, dt == nullptr, sres, npart))) return rc;
+  LAUNCH(k_dt_final, 1, W.smax, start_part(W), npart, 0, W.nflag, p->cfl, dt, W.dt, T.dt, W.stop,
+         (long long*)nullptr);
   if (p->emf_compute == CTMHD_EMF_B25A) {
     LAUNCH((k_prim<double, kB25A>), nb, T.S0, G, W0, p->gamma, W.stop);
     if constexpr (first_step_stored(kB25A, RECON))
@@ -1171,8 +1168,9 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
   }
   if ((rc = launch_faces<double, RECON>(st, p, T.S0, G, W0, FP, 0, nullptr))) return rc;
   if ((rc = launch_emf<double, RECON>(st, p, T.S0, G, W0, 0))) return rc;
-  LAUNCH(k_update<double>, nblocks(ninter), T.S0, T.S0, T.S1, G, W0, 0, 0, U,
-         (long long*)nullptr, 0, W.stop);
+  if ((rc = launch_update<double, 0>(st, nblocks(ninter), T.S0, T.S0, T.S1, G, W0, 0, U, nullptr,
+                                     0)))
+    return rc;
   if (p->emf_compute == CTMHD_EMF_B25A) {
     LAUNCH((k_prim<double, kB25A>), nb, T.S1, G, W1, p->gamma, W.stop);
     if constexpr (first_step_stored(kB25A, RECON))
@@ -1185,9 +1183,7 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
   if ((rc = launch_faces<double, RECON>(st, p, T.S1, G, W1, FP, 1, nullptr))) return rc;
   if ((rc = launch_emf<double, RECON>(st, p, T.S1, G, W1, 1))) return rc;
   // a stopped step (non-finite dt) leaves the caller's state as it was
-  LAUNCH(k_update<double>, nblocks(ninter), T.S0, T.S1, user, G, W1, 1, 0, U,
-         (long long*)nullptr, 0, W.stop);
-  return CTMHD_OK;
+  return launch_update<double, 0>(st, nblocks(ninter), T.S0, T.S1, user, G, W1, 1, U, nullptr, 0);
 }
 
 template <int RECON>

@@ -399,22 +399,30 @@ int phase_items(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, bool le
   return CTMHD_OK;
 }
 
+// Workgroups of the phases that most boxes have no work in (k_bsparse): four
+// per CU.
+constexpr int kSparseBlocks = 1024;
+
 template <typename T, int RECON, int RIEMANN, int EMF>
 int launch_bphase(hipStream_t st, int kind, long long items, const BatchArgs<T>& A, int q) {
   if (items <= 0) return CTMHD_OK;
   const unsigned grid = (unsigned)items;
+  const unsigned few = items < kSparseBlocks ? (unsigned)items : (unsigned)kSparseBlocks;
   switch (kind) {
     case PH_P: LAUNCH((k_bphase<T, kPC, kHLLD, EMF, PH_P>), grid, A, q); break;
     case PH_FIRST: LAUNCH((k_bphase<T, RECON, kHLLD, EMF, PH_FIRST>), grid, A, q); break;
     case PH_F: LAUNCH((k_bphase<T, RECON, RIEMANN, kQ26, PH_F>), grid, A, q); break;
     case PH_E: LAUNCH((k_bphase<T, RECON, kHLLD, EMF, PH_E>), grid, A, q); break;
-    case PH_U:
-    case PH_X: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_U>), grid, A, q); break;
-    case PH_O: LAUNCH((k_bphase<T, kPC, kHLLD, EMF, PH_O>), grid, A, q); break;
+    case PH_U: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_U>), grid, A, q); break;
+    case PH_X: LAUNCH((k_bsparse<T, kQ26, PH_X>), few, A, q); break;
+    case PH_O: LAUNCH((k_bsparse<T, EMF, PH_O>), few, A, q); break;
     case PH_WRAP: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_WRAP>), grid, A, q); break;
-    case PH_DT: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_DT>), grid, A, q); break;
+    case PH_DT:
+      // the CFL maxima of independent boxes are formed by PH_WRAP
+      if (A.level) LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_DT>), grid, A, q);
+      break;
     case PH_XCHG: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_XCHG>), grid, A, q); break;
-    default: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_COPY>), grid, A, q); break;
+    default: LAUNCH((k_bsparse<T, kQ26, PH_COPY>), few, A, q); break;
   }
   return CTMHD_OK;
 }
@@ -466,8 +474,11 @@ int batched_run(const ctmhd_params* p, int nbox, const ctmhd_box* boxes, const L
     return CTMHD_OK;
   };
   const int ndt = A.dt_per_box ? nbox : 1;
-  LAUNCH(k_breset, 1, nbox, nphase, A.done, A.cursor, 1, A.stop, A.err, (int*)A.loc, A.slots,
-         A.nflag);
+  A.want_dt = dt_fixed ? 0 : 1;
+  // an odd number of steps starts from a copy in B, so that the last one ends
+  // in the caller's arrays
+  LAUNCH(k_breset, 1, nbox, nphase, A.done, A.cursor, 1, A.stop, A.err, (int*)A.loc, nsteps & 1,
+         A.slots, A.nflag);
   LAUNCH(k_btab<T>, (nbox + kBlock - 1) / kBlock, A, nbox);
   if ((rc = run_launch(0))) return rc;
   for (int n = 0; n < nsteps; ++n) {
@@ -480,7 +491,7 @@ int batched_run(const ctmhd_params* p, int nbox, const ctmhd_box* boxes, const L
     LAUNCH(k_bstep_end, 1, (int*)A.loc, A.stop, A.err, dg);
   }
   if (persistent)
-    LAUNCH(k_breset, 1, nbox, nphase, A.done, A.cursor, 0, A.stop, A.err, (int*)A.loc, A.slots,
+    LAUNCH(k_breset, 1, nbox, nphase, A.done, A.cursor, 0, A.stop, A.err, (int*)A.loc, 0, A.slots,
            A.nflag);
   A.diag = nullptr;
   return run_launch(2);

@@ -199,6 +199,42 @@ inline void prof_end(hipStream_t st) {
     if (hipGetLastError() != hipSuccess) return fail(CTMHD_EHIP, "kernel launch failed: " #kern); \
   } while (0)
 
+// Workgroups of the first-order, fix-up and copy-back launches, which stride
+// over the box: enough to fill the chip when there is work, few enough that
+// the usual launch that finds none costs microseconds.
+inline int fix_blocks(int ninter) {
+  const int nb = nblocks(ninter);
+  return nb < 2048 ? nb : 2048;
+}
+
+// The update of one stage: main pass (fixup 0) or fix-up.  Each form is a
+// kernel of its own, so that none carries the registers of the others.
+template <typename T, int fixup>
+int launch_update(hipStream_t st, int blocks, State base, State half, State out, const Geom& G,
+                  const Work<T>& W, int stage, const UpdateCfg& U, long long* diag, int band) {
+  if (stage == 0)
+    LAUNCH((k_update<T, 0, fixup>), blocks, base, half, out, G, W, U, diag, band, W.stop);
+  else
+    LAUNCH((k_update<T, 1, fixup>), blocks, base, half, out, G, W, U, diag, band, W.stop);
+  return CTMHD_OK;
+}
+
+// Partial CFL maxima of k_start: in the edge EMFs, which are not yet in use.
+template <typename T>
+unsigned long long* start_part(const Work<T>& W) {
+  return (unsigned long long*)W.E[0][0];
+}
+
+// The start of a call on one box: the caller's state `user` with its ghost
+// layers into A (copy: another buffer) and npart partial CFL maxima.
+template <typename T>
+int launch_start(hipStream_t st, const ctmhd_params* p, State user, State A, bool copy,
+                 const Geom& G, const Work<T>& W, bool want_dt, double sres, int& npart) {
+  npart = fix_blocks(G.elems);
+  LAUNCH(k_start, npart, user, A, copy ? 1 : 0, G, p->gamma, sres, want_dt ? 1 : 0, start_part(W));
+  return CTMHD_OK;
+}
+
 // Launch shape of the face pass when the tile knob leaves it open, from the
 // faces of the two marching directions of all boxes of a call: chunks of 32
 // faces (16 in a call of many boxes, whose marches are of uneven length) once
