@@ -390,8 +390,7 @@ int phase_items(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, bool le
   for (int q = 0; q < nphase; ++q) items[q] = 0;
   for (int b = 0; b < nbox; ++b) {
     const Geom G = make_geom(boxes[b]);
-    const FacePlan FP = make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p),
-                                       !level, faces, nbox);
+    const FacePlan FP = make_face_plan(G, p, !level, faces, nbox, false);
     for (int q = 0; q < nphase; ++q) items[q] += item_count(kind[q], G, FP, per, level);
   }
   for (int q = 0; q < nphase; ++q)
@@ -612,8 +611,7 @@ int build_plan(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, const Le
     const ctmhd_box& bx = boxes[b];
     BoxDesc& d = desc[b];
     d.G = make_geom(bx);
-    d.FP = make_face_plan(d.G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p), !L, faces,
-                         nbox);
+    d.FP = make_face_plan(d.G, p, !L, faces, nbox, false);
     d.off = bx.offset;
     d.flag_off = L ? bx.offset : flag_off;  // a level indexes flags by storage position
     flag_off += box_inter_ll(bx);

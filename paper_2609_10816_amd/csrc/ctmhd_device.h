@@ -52,6 +52,24 @@ __device__ __forceinline__ int gidx() { return blockIdx.x * blockDim.x + threadI
 // compiler fold x-neighbour offsets into the load instructions.
 __device__ __forceinline__ int gstride(const Geom& G, int d) { return d == 0 ? 1 : G.st[d]; }
 
+// Element s of a field array, addressed by a 32-bit byte offset (a box has
+// less than 2^31 / 6 elements, so the offset of a double fits): the array's
+// base stays in scalar registers and all arrays read at one position share one
+// offset register, where a signed element index costs a 64-bit address per
+// array (two registers and an add).
+template <typename T>
+__device__ __forceinline__ T& at(T* p, int s) {
+  using B = typename std::conditional<std::is_const<T>::value, const char, char>::type;
+  return *reinterpret_cast<T*>(reinterpret_cast<B*>(p) + (unsigned)s * (unsigned)sizeof(T));
+}
+
+// The element k positions along axis d from s (k a constant): x neighbours are
+// immediate offsets of the load.
+template <typename T>
+__device__ __forceinline__ T& nbr(T* p, const Geom& G, int s, int d, int k) {
+  return d == 0 ? at(p + k, s) : at(p, s + k * G.st[d]);
+}
+
 // Workgroups are dispatched to the 8 XCDs of the chip round-robin (workgroup
 // i on XCD i mod 8), and each XCD has its own L2.  This permutation of the
 // tiles of a launch gives each XCD a contiguous run of them, so that the
@@ -80,6 +98,9 @@ __device__ __forceinline__ int xcd_band_tile(int m) {
   const int k = b / kXcds;
   return (k / m) * C + (b % kXcds) * m + k % m;
 }
+
+// the constant address space
+#define CTMHD_CONST __attribute__((address_space(4)))
 
 struct State {
   double* c[5];
@@ -151,11 +172,11 @@ struct CellRaw {
 
 __device__ __forceinline__ void cell_load(const State& S, const Geom& G, int s, CellRaw& R) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) R.c[m] = S.c[m][s];
+  for (int m = 0; m < 5; ++m) R.c[m] = at(S.c[m], s);
 #pragma unroll
   for (int d = 0; d < 3; ++d) {
-    R.bl[d] = S.b[d][s];
-    R.bh[d] = S.b[d][s + G.st[d]];
+    R.bl[d] = at(S.b[d], s);
+    R.bh[d] = nbr(S.b[d], G, s, d, 1);
   }
 }
 
@@ -427,8 +448,13 @@ struct FacePlan {
   int xw, xlen, xwaves, xrows, xblocks;  // xwaves = items; xrows items per wavefront
   int xdx, xdy, xdz;  // step of one item (64 - 2r - 1 cells) in (cell, row y, row z)
   // y and z parts: lane blocks x chunks
-  int chunk[3], nchunk[3], lanes[3], lblocks[3], blocks[3];
-  int total_blocks;
+  int chunk[3], lanes[3], blocks[3];
+  // The box is cut into nby x nbz bricks of wy x wz whole rows (ranges in y and
+  // z), each with all three parts of its faces, and cy / cz chunks of the y / z
+  // marches: a large box's state then comes from HBM about once, not once per
+  // direction.
+  int nby, nbz, wy, wz, cy, cz;
+  int brick_blocks, total_blocks;
 };
 
 // Face-local primitive of a cell for the face normal a (FP64 recovery, then T).
@@ -500,13 +526,13 @@ template <typename T>
 __device__ __forceinline__ void store_flux(const Work<T>& W, int s, int a, int stage,
                                            const FaceOut<T>& o) {
 #pragma unroll
-  for (int m = 0; m < 5; ++m) __builtin_nontemporal_store(o.F[m], &W.F[stage][a][m][s]);
+  for (int m = 0; m < 5; ++m) __builtin_nontemporal_store(o.F[m], &at(W.F[stage][a][m], s));
 }
 template <typename T>
 __device__ __forceinline__ void store_speeds(const Work<T>& W, int s, int a, const FaceOut<T>& o) {
-  __builtin_nontemporal_store(o.ap, &W.ap[a][s]);
-  __builtin_nontemporal_store(o.am, &W.am[a][s]);
-  __builtin_nontemporal_store(o.us, &W.us[a][s]);
+  __builtin_nontemporal_store(o.ap, &at(W.ap[a], s));
+  __builtin_nontemporal_store(o.am, &at(W.am[a], s));
+  __builtin_nontemporal_store(o.us, &at(W.us[a], s));
 }
 
 // Periodic copies p + m n_d, m in [mlo, mhi], of coordinate p of a solved x_a
@@ -606,12 +632,12 @@ __device__ __forceinline__ void cell_tfaces(const CellRaw& R, int a, double t[4]
 // joule_pair takes them.
 __device__ __forceinline__ void face_nb(const State& S, const Geom& G, int s, int a,
                                         double nb[4]) {
-  const int sb = gstride(G, (a + 1) % 3), sc = gstride(G, (a + 2) % 3);
+  const int b = (a + 1) % 3, c = (a + 2) % 3;
   const double* ba = S.b[a];
-  nb[0] = ba[s - sb];
-  nb[1] = ba[s + sb];
-  nb[2] = ba[s - sc];
-  nb[3] = ba[s + sc];
+  nb[0] = nbr(ba, G, s, b, -1);
+  nb[1] = nbr(ba, G, s, b, 1);
+  nb[2] = nbr(ba, G, s, c, -1);
+  nb[3] = nbr(ba, G, s, c, 1);
 }
 
 // Value of the neighbouring lane (l - 1 for lane_prev, l + 1 for lane_next)
@@ -667,7 +693,8 @@ __device__ __forceinline__ void recon_lanes(T q, T& qm, T& qp) {
 // n = 8 (13%).
 template <typename T, int RECON, int RIEMANN>
 __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const FacePlan& FP,
-                        int wave, int stage, double gamma, double eta, int& nfb) {
+                        int y0, int z0, int wave, int stage, double gamma, double eta,
+                        int& nfb) {
   constexpr int r = recon_halfwidth(RECON);
   const int lane = threadIdx.x & 63;
   // this wavefront takes items [it, end) and loads the cells of the next item
@@ -675,26 +702,27 @@ __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const F
   int it = wave * FP.xrows;
   const int end = it + FP.xrows < FP.xwaves ? it + FP.xrows : FP.xwaves;
   // lane's cell: position x of extended row (y, z), all counted from the
-  // start of their ranges; lanes past the end of the line stay on its last row
+  // start (y0, z0) of the brick's ranges; lanes past them stay on the last row
   int x, y, z;
   {
     const int e = it * (63 - 2 * r) + lane;
     const int row = e / FP.xw;
     x = e - row * FP.xw;
-    z = row / FP.tlen[1];
-    y = row - z * FP.tlen[1];
+    z = row / FP.wy;
+    y = row - z * FP.wy;
   }
+  const int ymax = FP.tlen[1] - 1 - y0, zmax = (FP.wz < FP.tlen[2] - z0 ? FP.wz : FP.tlen[2] - z0) - 1;
   auto locate = [&](int s3[3]) {
-    const bool in = z < FP.tlen[2];
     s3[0] = FP.lo[0] - (r + 1) + x;
-    s3[1] = FP.tlo + (in ? y : FP.tlen[1] - 1);
-    s3[2] = FP.tlo + (in ? z : FP.tlen[2] - 1);
+    s3[1] = FP.tlo + y0 + (y < ymax ? y : ymax);
+    s3[2] = FP.tlo + z0 + (z < zmax ? z : zmax);
     return s3[0] + G.st[1] * s3[1] + G.st[2] * s3[2];
   };
   // whether this lane resolves a face: it holds a face position and its
   // stencil lies in the wavefront
   auto is_face = [&]() {
-    return lane >= r + 1 && lane <= 63 - r && x >= r + 1 && x <= r + FP.nf[0] && z < FP.tlen[2];
+    return lane >= r + 1 && lane <= 63 - r && x >= r + 1 && x <= r + FP.nf[0] && y <= ymax &&
+           z <= zmax;
   };
   // whether this lane's face of an item needs the Joule flux; if so its
   // normal-field neighbours are loaded with the item's cell
@@ -726,8 +754,8 @@ __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const F
         x -= FP.xw;
         ++y;
       }
-      if (y >= FP.tlen[1]) {
-        y -= FP.tlen[1];
+      if (y >= FP.wy) {
+        y -= FP.wy;
         ++z;
       }
       sn = locate(n3);
@@ -761,14 +789,16 @@ __device__ void faces_x(const State& S, const Geom& G, const Work<T>& W, const F
 // per cell); each cell is loaded and reconstructed once.
 template <typename T, int RECON, int RIEMANN, int A>
 __device__ void faces_march(const State& S, const Geom& G, const Work<T>& W, const FacePlan& FP,
-                            int lblock, int chunk, int stage, double gamma, double eta, int& nfb) {
+                            int c0, int lblock, int chunk, int stage, double gamma, double eta,
+                            int& nfb) {
   constexpr int r = recon_halfwidth(RECON);
   const int lane = lblock * kBlock + threadIdx.x;
   if (lane >= FP.lanes[A]) return;
   const int C = A == 1 ? 2 : 1;  // transverse axes: x (fastest) and C
   int s3[3];
   s3[0] = FP.tlo + lane % FP.tlen[0];
-  s3[C] = FP.tlo + lane / FP.tlen[0];
+  s3[C] = FP.tlo + c0 + lane / FP.tlen[0];
+  if (s3[C] >= FP.tlo + FP.tlen[C] || chunk * FP.chunk[A] >= FP.nf[A]) return;  // outside the box
   const int f0 = FP.lo[A] + chunk * FP.chunk[A];
   int f1 = f0 + FP.chunk[A];
   if (f1 > FP.lo[A] + FP.nf[A]) f1 = FP.lo[A] + FP.nf[A];
@@ -804,7 +834,7 @@ __device__ void faces_march(const State& S, const Geom& G, const Work<T>& W, con
     const bool jq = j_next;
     if (q < f1 - 1 + r) {
       cell_load(S, G, base + (q + 1) * sa, nxt);
-      if (q + 1 - r >= f0) bn_next = S.b[A][base + (q + 1 - r) * sa];
+      if (q + 1 - r >= f0) bn_next = at(S.b[A], base + (q + 1 - r) * sa);
       j_next = false;
       if (eta > 0.0 && q + 1 >= f0 && q + 1 < f1) {
         s3[A] = q + 1;
@@ -840,29 +870,51 @@ template <typename T, int RECON, int RIEMANN>
 __device__ __forceinline__ void faces_block(const State& S, const Geom& G, const Work<T>& W,
                                             const FacePlan& FP, int b, int stage, double gamma,
                                             double eta, int& nfb) {
+  const int brick = b / FP.brick_blocks;
+  b -= brick * FP.brick_blocks;
+  const int iz = brick / FP.nby, iy = brick - iz * FP.nby;
+  const int y0 = iy * FP.wy, z0 = iz * FP.wz;
   // long-running marching blocks first, the short x-face wavefronts fill in
   if (b < FP.blocks[2]) {
-    faces_march<T, RECON, RIEMANN, 2>(S, G, W, FP, b / FP.nchunk[2], b % FP.nchunk[2], stage,
+    faces_march<T, RECON, RIEMANN, 2>(S, G, W, FP, y0, b / FP.cz, iz * FP.cz + b % FP.cz, stage,
                                       gamma, eta, nfb);
   } else if ((b -= FP.blocks[2]) < FP.blocks[1]) {
-    faces_march<T, RECON, RIEMANN, 1>(S, G, W, FP, b / FP.nchunk[1], b % FP.nchunk[1], stage,
+    faces_march<T, RECON, RIEMANN, 1>(S, G, W, FP, z0, b / FP.cy, iy * FP.cy + b % FP.cy, stage,
                                       gamma, eta, nfb);
   } else {
     b -= FP.blocks[1];
     const int wave = b * (kBlock / 64) + (threadIdx.x >> 6);
     if (wave * FP.xrows < FP.xwaves)
-      faces_x<T, RECON, RIEMANN>(S, G, W, FP, wave, stage, gamma, eta, nfb);
+      faces_x<T, RECON, RIEMANN>(S, G, W, FP, y0, z0, wave, stage, gamma, eta, nfb);
   }
 }
 
+template <typename T>
+struct FaceArgs {
+  State S;
+  Geom G;
+  Work<T> W;
+  FacePlan FP;
+  int stage;
+  double gamma, eta;
+  long long* diag;
+  const int* stop;
+};
+
+// The arguments are read where they are used, through the kernel argument
+// segment as constant memory: scalar loads inside the three parts.  As by-value
+// arguments the compiler loads all of them (about 60 pointers) at the top of
+// the kernel and spills what does not fit the scalar registers to vector lanes:
+// 24 to 38 v_readlane per face in the marches, one in 25 VALU instructions.
 template <typename T, int RECON, int RIEMANN>
-__global__ void __launch_bounds__(kBlock)
-    k_faces(State S, Geom G, Work<T> W, FacePlan FP, int stage, double gamma, double eta,
-            long long* diag, const int* stop) {
-  if (*stop) return;
+__global__ void __launch_bounds__(kBlock) k_faces(FaceArgs<T> byval) {
+  (void)byval;
+  const FaceArgs<T>& A =
+      *(const FaceArgs<T>*)(const CTMHD_CONST FaceArgs<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+  if (*A.stop) return;
   int nfb = 0;
-  faces_block<T, RECON, RIEMANN>(S, G, W, FP, blockIdx.x, stage, gamma, eta, nfb);
-  if (diag && nfb) atomicAdd((unsigned long long*)&diag[2], (unsigned long long)nfb);
+  faces_block<T, RECON, RIEMANN>(A.S, A.G, A.W, A.FP, blockIdx.x, A.stage, A.gamma, A.eta, nfb);
+  if (A.diag && nfb) atomicAdd((unsigned long long*)&A.diag[2], (unsigned long long)nfb);
 }
 
 // ---------------------------------------------------------------------------
@@ -1578,7 +1630,6 @@ struct BoxTab {
   FacePlan FP;
   double sres;
 };
-#define CTMHD_CONST __attribute__((address_space(4)))
 
 __device__ __forceinline__ State shift_state(const State& S, long long off) {
   State R;

@@ -263,15 +263,28 @@ long long march_faces(const ctmhd_box& b, int recon, int emf, bool periodic) {
   return (b.n[0] + t) * ((b.n[1] + e) * (b.n[2] + t) + (b.n[2] + e) * (b.n[1] + t));
 }
 
-// Face plan: ranges and launch shape of the fused face kernel.  chunk_min and
-// xrows: the tile knob's values, 0 automatic from `faces` (march_faces summed
-// over the nbox boxes of the call).
-FacePlan make_face_plan(const Geom& G, int recon, int emf, int chunk_min, int xrows, bool periodic,
-                        long long faces, int nbox) {
+// Bricks of the face pass: boxes whose state is larger than kBrickFrom are cut
+// into bricks of about kBrickBytes, so that the three parts of a brick read it
+// from the 256 MB Infinity Cache after the first.  Measured per launch, without
+// and with: FP32 PPM 160^3 (0.3 GB) 396 / 404 us, 200^3 814 / 742, 256^3 1601 /
+// 1354, 384^3 5264 / 4670; FP64 PLM 256^3 1947 / 1755; FP64 PC 384^3 6143 /
+// 5580.  FP64 PPM with HLLD is held up by its arithmetic instead (256^3 2088 /
+// 2082, 512^3 16.40 / 16.50 ms), and keeps one brick, whose long marches all
+// start first.
+constexpr long long kBrickFrom = 384LL << 20, kBrickBytes = 64LL << 20;
+// Face plan: ranges and launch shape of the fused face kernel.  What the tile
+// knob leaves open is chosen from `faces`, march_faces summed over the nbox
+// boxes of the call.
+// (bricks: the box may be cut.  The plan of a batch serves every precision and
+// solver, so it does not depend on them: its boxes stay whole.)
+FacePlan make_face_plan(const Geom& G, const ctmhd_params* p, bool periodic, long long faces,
+                        int nbox, bool bricks) {
+  const int emf = p->emf_compute;
+  int chunk_min = tile_chunk(p), xrows = tile_xrows(p);
   if (chunk_min <= 0) chunk_min = auto_face_chunk(faces, nbox);
   if (xrows <= 0) xrows = auto_face_xrows(faces);
   FacePlan P;
-  const int r = recon_halfwidth(recon);
+  const int r = recon_halfwidth(p->recon);
   const int g = G.g;
   // Q26 reconstructs u* along the transverse axes to the edges, which needs
   // faces r+1 beyond the edge range [g, g+n]; the other schemes only need
@@ -290,64 +303,79 @@ FacePlan make_face_plan(const Geom& G, int recon, int emf, int chunk_min, int xr
     P.ulo[d] = g;
     P.ulen[d] = G.n[d];
   }
-  // x part
-  const int xstep = 64 - 2 * r - 1;
-  P.xw = P.nf[0] + 2 * r + 1;
-  P.xlen = P.xw * P.tlen[1] * P.tlen[2];
-  P.xwaves = (P.xlen - 2 * r - 1 + xstep - 1) / xstep;
-  P.xdx = xstep % P.xw;
-  P.xdy = xstep / P.xw % P.tlen[1];
-  P.xdz = xstep / P.xw / P.tlen[1];
-  P.xrows = xrows;
-  const int xwf = (P.xwaves + xrows - 1) / xrows;  // wavefronts of the x part
-  P.xblocks = (xwf + kBlock / 64 - 1) / (kBlock / 64);
-  // y and z parts: enough chunks along the march for ~8192 waves in flight
-  P.total_blocks = P.xblocks;
+  // marches: enough chunks for ~8192 waves in flight
+  int nchunk[3] = {0, 0, 0};
   for (int A = 1; A <= 2; ++A) {
     const int C = A == 1 ? 2 : 1;
-    P.lanes[A] = P.tlen[0] * P.tlen[C];
-    P.lblocks[A] = (P.lanes[A] + kBlock - 1) / kBlock;
-    int want = (8192 * 64 / kBlock) / (P.lblocks[A] > 0 ? P.lblocks[A] : 1);
+    const int lblocks = (P.tlen[0] * P.tlen[C] + kBlock - 1) / kBlock;
+    int want = (8192 * 64 / kBlock) / (lblocks > 0 ? lblocks : 1);
     int maxch = (P.nf[A] + chunk_min - 1) / chunk_min;  // chunk >= chunk_min faces (warm-up 2r+1)
     if (want > maxch) want = maxch;
     if (want < 1) want = 1;
     P.chunk[A] = (P.nf[A] + want - 1) / want;
-    P.nchunk[A] = (P.nf[A] + P.chunk[A] - 1) / P.chunk[A];
-    P.blocks[A] = P.lblocks[A] * P.nchunk[A];
-    P.total_blocks += P.blocks[A];
+    nchunk[A] = (P.nf[A] + P.chunk[A] - 1) / P.chunk[A];
   }
-  P.chunk[0] = P.nchunk[0] = P.lanes[0] = P.lblocks[0] = P.blocks[0] = 0;
+  P.chunk[0] = P.lanes[0] = P.blocks[0] = 0;
+  // bricks
+  P.nby = P.nbz = 1;
+  const long long bytes = 64LL * G.elems;
+  if (bytes > kBrickFrom && bricks) {
+    P.nbz = nchunk[2];
+    const long long slab = bytes / P.nbz;
+    P.nby = (int)((slab + kBrickBytes - 1) / kBrickBytes);
+    if (P.nby > nchunk[1]) P.nby = nchunk[1];
+    if (P.nby < 1) P.nby = 1;
+  }
+  P.wy = (P.tlen[1] + P.nby - 1) / P.nby;
+  P.wz = (P.tlen[2] + P.nbz - 1) / P.nbz;
+  P.cy = (nchunk[1] + P.nby - 1) / P.nby;
+  P.cz = (nchunk[2] + P.nbz - 1) / P.nbz;
+  P.lanes[1] = P.tlen[0] * P.wz;
+  P.lanes[2] = P.tlen[0] * P.wy;
+  P.blocks[1] = (P.lanes[1] + kBlock - 1) / kBlock * P.cy;
+  P.blocks[2] = (P.lanes[2] + kBlock - 1) / kBlock * P.cz;
+  // x part of a brick
+  const int xstep = 64 - 2 * r - 1;
+  P.xw = P.nf[0] + 2 * r + 1;
+  P.xlen = P.xw * P.wy * P.wz;
+  P.xwaves = (P.xlen - 2 * r - 1 + xstep - 1) / xstep;
+  P.xdx = xstep % P.xw;
+  P.xdy = xstep / P.xw % P.wy;
+  P.xdz = xstep / P.xw / P.wy;
+  P.xrows = xrows;
+  const int xwf = (P.xwaves + xrows - 1) / xrows;  // wavefronts of the x part
+  P.xblocks = (xwf + kBlock / 64 - 1) / (kBlock / 64);
+  P.brick_blocks = P.blocks[1] + P.blocks[2] + P.xblocks;
+  P.total_blocks = P.brick_blocks * P.nby * P.nbz;
   return P;
 }
 
 // The face plan of a single periodic box.
 FacePlan box_face_plan(const ctmhd_params* p, const ctmhd_box& b, const Geom& G) {
-  return make_face_plan(G, p->recon, p->emf_compute, tile_chunk(p), tile_xrows(p), true,
-                        march_faces(b, p->recon, p->emf_compute, true), 1);
+  const bool alu = p->precision == CTMHD_FP64 && p->recon == CTMHD_RECON_PPM &&
+                   p->riemann == CTMHD_RIEMANN_HLLD;
+  return make_face_plan(G, p, true, march_faces(b, p->recon, p->emf_compute, true), 1, !alu);
 }
 
 template <typename T, int RECON>
 int launch_faces(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, const Work<T>& W,
                  const FacePlan& FP, int stage, long long* diag) {
+  const FaceArgs<T> A{S, G, W, FP, stage, p->gamma, p->eta, diag, W.stop};
   prof_begin(st);
   if constexpr (std::is_same<T, float>::value) {
     if (p->precision == CTMHD_FP32_R64) {
       if (p->riemann == CTMHD_RIEMANN_HLLD)
-        LAUNCH((k_faces<T, RECON, kHLLD64>), FP.total_blocks, S, G, W, FP, stage, p->gamma, p->eta,
-               diag, W.stop);
+        LAUNCH((k_faces<T, RECON, kHLLD64>), FP.total_blocks, A);
       else
-        LAUNCH((k_faces<T, RECON, kLLF64>), FP.total_blocks, S, G, W, FP, stage, p->gamma, p->eta,
-               diag, W.stop);
+        LAUNCH((k_faces<T, RECON, kLLF64>), FP.total_blocks, A);
       prof_end(st);
       return CTMHD_OK;
     }
   }
   if (p->riemann == CTMHD_RIEMANN_HLLD)
-    LAUNCH((k_faces<T, RECON, kHLLD>), FP.total_blocks, S, G, W, FP, stage, p->gamma, p->eta, diag,
-           W.stop);
+    LAUNCH((k_faces<T, RECON, kHLLD>), FP.total_blocks, A);
   else
-    LAUNCH((k_faces<T, RECON, kLLF>), FP.total_blocks, S, G, W, FP, stage, p->gamma, p->eta, diag,
-           W.stop);
+    LAUNCH((k_faces<T, RECON, kLLF>), FP.total_blocks, A);
   prof_end(st);
   return CTMHD_OK;
 }

@@ -61,3 +61,16 @@ def test_launch_shape_same_bits(shape):
     one = _run(shape, **kw)
     for chunk, xrows in ((1, 1), (3, 2), (7, 5), (64, 64)):
         _same(one, _run(shape, tile=ctmhd.make_tile(chunk=chunk, xrows=xrows), **kw))
+
+
+def test_bricks_same_bits():
+    """A box whose state exceeds the size from which the face pass is cut into
+    bricks (ragged, so that edge bricks are partial), against the same box as a
+    level of one box, which is not cut."""
+    shape = (150, 170, 262)
+    cons, bf, info = inputs.turbulent_box(shape, mach=2.0, b0=(0.5, 0.3, -0.2), db_rms=0.2,
+                                          seed_v=83, seed_a=84)
+    dx = [1.0 / 128.0] * 3
+    P = ctmhd.make_params(recon="plm", emf="q26", eta=1e-3)
+    _same(ctmhd.run(P, cons, bf, dx, 1),
+          ctmhd.run_level(P, cons, bf, dx, [(0, n) for n in shape], 1))
