@@ -314,6 +314,8 @@ int batch_args(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, void* ws
   for (int v = 0; v < 3; ++v)
     for (int d = 0; d < 3; ++d) W.fsf[v][d][0] = W.fsf[v][d][1] = nullptr;
   const bool first = first_step_stored(p->emf_compute, p->recon);
+  A.wbase = (T*)cv.p;
+  A.wstride = (long long)(align256(e * sizeof(T)) / sizeof(T));
   if (p->emf_compute == CTMHD_EMF_B25A) {
     for (int c = 0; c < 3; ++c) W.ecell[c] = cv.take<T>(e);
     if (first)
@@ -336,6 +338,7 @@ int batch_args(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, void* ws
   for (int a = 0; a < 3; ++a) W.us[a] = cv.take<T>(e);
   for (int st = 0; st < 2; ++st)
     for (int c = 0; c < 3; ++c) W.E[st][c] = cv.take<T>(e);
+  A.narr = (int)(((T*)cv.p - A.wbase) / A.wstride);
   W.flag = cv.take<uint8_t>(e);
   A.done = cv.take<int>((size_t)nphase * nbox);
   A.nflag = cv.take<int>(4 * (size_t)nbox);
