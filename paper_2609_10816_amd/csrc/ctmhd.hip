@@ -4,15 +4,16 @@
 // is a short sequence of stream-ordered kernels on a ghosted box:
 //   k_start      once per call: ghost fill, CFL maximum and, for an odd number
 //                of steps, the copy into the other buffer
-//   k_dt_final   dt from the CFL maximum of the step's starting state (or the
-//                caller's dt); a non-finite dt stops the call
 //   per stage:
 //   k_faces      reconstruction + Riemann solve at every face of all three
 //                directions in one launch: x faces inside a wavefront (cross-
 //                lane shuffles), y and z faces by marching along the face
 //                normal with a register window, so that every cell is loaded
 //                and reconstructed once per direction; primitives are formed
-//                on the fly (pressure recovery in FP64)
+//                on the fly (pressure recovery in FP64); in the first stage an
+//                extra workgroup forms dt from the CFL maximum of the step's
+//                starting state (or takes the caller's); a non-finite dt stops
+//                the call
 //   k_emf_march  Q26 edge EMFs of the three edge directions with LD04
 //                averaging and eta j, one thread per column of edges marching
 //                up z (the z reconstructions streamed through registers)
@@ -50,7 +51,7 @@ int launch_fo(hipStream_t st, const ctmhd_params* p, State Sn, const Geom& G, co
 template <typename T, int RECON>
 int run_stage(hipStream_t st, const ctmhd_params* p, const Geom& G, const Work<T>& W,
               const FacePlan& FP, State in, State base, State out, int stage, double sres,
-              long long* diag) {
+              long long* diag, const Restore& R, const DtStep* dt) {
   int rc;
   if (p->emf_compute == CTMHD_EMF_B25A) {
     LAUNCH((k_prim<T, kB25A>), nblocks(G.elems), in, G, W, p->gamma, W.stop);
@@ -61,7 +62,7 @@ int run_stage(hipStream_t st, const ctmhd_params* p, const Geom& G, const Work<T
     if constexpr (first_step_stored(kFS18, RECON))
       LAUNCH((k_first_step<T, RECON, kFS18>), nblocks(G.elems), G, W, W.stop);
   }
-  if ((rc = launch_faces<T, RECON>(st, p, in, G, W, FP, stage, diag))) return rc;
+  if ((rc = launch_faces<T, RECON>(st, p, in, G, W, FP, stage, diag, dt))) return rc;
   if ((rc = launch_emf<T, RECON>(st, p, in, G, W, stage))) return rc;
   const int ninter = G.n[0] * G.n[1] * G.n[2];
   UpdateCfg U;
@@ -72,11 +73,12 @@ int run_stage(hipStream_t st, const ctmhd_params* p, const Geom& G, const Work<T
   U.force = p->force_flags ? p->force_flags + (size_t)stage * ninter : nullptr;
   U.flag_storage = 0;
   const int band = xcd_band(p, (long long)G.n[0] * G.n[1], ninter);
-  if ((rc = launch_update<T, 0>(st, nblocks(ninter), base, in, out, G, W, stage, U, diag, band)))
+  if ((rc = launch_update<T, 0>(st, nblocks(ninter), base, in, out, G, W, stage, U, diag, band,
+                                p->fofc ? Restore{} : R)))
     return rc;
   if (!p->fofc) return CTMHD_OK;
   if ((rc = launch_fo<T>(st, p, base, G, W, stage, ninter))) return rc;
-  return launch_update<T, 1>(st, fix_blocks(ninter), base, in, out, G, W, stage, U, diag, band);
+  return launch_update<T, 1>(st, fix_blocks(ninter), base, in, out, G, W, stage, U, diag, band, R);
 }
 
 template <typename T, int RECON>
@@ -101,20 +103,21 @@ int step_box(const ctmhd_params* p, const ctmhd_box* box, double* const cons[5],
   if (odd) B = user;
   const State other = odd ? A : B;
   int npart = 0;
-  if ((rc = launch_start(st, p, user, A, odd, G, W, dt_fixed == nullptr, sres, npart))) return rc;
+  if ((rc = launch_start(st, p, user, A, odd, G, W, dt_fixed == nullptr, sres,
+                         (long long*)diag, diag ? 4 * nsteps : 0, npart)))
+    return rc;
   for (int n = 0; n < nsteps; ++n) {
     long long* dg = diag ? (long long*)diag + 4 * n : nullptr;
-    LAUNCH(k_dt_final, 1, W.smax, start_part(W), npart, n, W.nflag, p->cfl,
-           dt_fixed ? dt_fixed + n : nullptr, W.dt, dt_out ? dt_out + n : nullptr, W.stop, dg);
-    if ((rc = run_stage<T, RECON>(st, p, G, W, FP, A, A, H, 0, sres, dg))) return rc;
-    if ((rc = run_stage<T, RECON>(st, p, G, W, FP, H, A, B, 1, sres, dg))) return rc;
+    const DtStep D = make_dt_step(p, W, npart, n, dt_fixed ? dt_fixed + n : nullptr,
+                                  dt_out ? dt_out + n : nullptr, dg);
+    if ((rc = run_stage<T, RECON>(st, p, G, W, FP, A, A, H, 0, sres, dg, Restore{}, &D))) return rc;
+    // the last kernel of the call brings a stopped call's state back
+    const Restore R{user, other, G.elems, n == nsteps - 1 ? nsteps : 0};
+    if ((rc = run_stage<T, RECON>(st, p, G, W, FP, H, A, B, 1, sres, dg, R, nullptr))) return rc;
     State tmp = A;
     A = B;
     B = tmp;
   }
-  // a stopped call may have left its state in the other buffer (a capped grid:
-  // the launch almost always finds nothing to do)
-  LAUNCH(k_restore, fix_blocks(G.elems), user, other, G.elems, nsteps, W.stop);
   return CTMHD_OK;
 }
 

@@ -1109,9 +1109,10 @@ int adjoint_box(const ctmhd_params* p_in, const ctmhd_box* box, const double* co
   State A = C.A, H = C.H;
   // forward: S0 with ghosts, the caller's dt, stage 1 into H = S1
   int npart = 0;
-  if ((rc = launch_start(st, p, S0, A, true, G, W, false, 0.0, npart))) return rc;
-  LAUNCH(k_dt_final, 1, W.smax, start_part(W), 0, 0, W.nflag, p->cfl, dt, W.dt, (double*)nullptr,
-         W.stop, (long long*)nullptr);
+  if ((rc = launch_start(st, p, S0, A, true, G, W, false, 0.0, nullptr, 0, npart))) return rc;
+  // a non-finite dt must stop the passes before the update too: they are
+  // reversed from what the face pass leaves
+  LAUNCH(k_dt_final, 1, make_dt_step(p, W, npart, 0, dt, nullptr, nullptr));
   if ((rc = launch_faces<double, RECON>(st, p, A, G, W, FP, 0, nullptr))) return rc;
   LAUNCH(k_adj_save9, nb, G, W, C.W0);
   if constexpr (EMF != kQ26) LAUNCH((k_prim<double, EMF>), nb, A, G, W, p->gamma, W.stop);
@@ -1154,9 +1155,9 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
   const double dxmin = fmin(G.dx[0], fmin(G.dx[1], G.dx[2]));
   const double sres = p->eta > 0.0 ? 2.0 * p->eta / (dxmin * dxmin) : 0.0;
   int npart = 0;
-  if ((rc = launch_start(st, p, user, T.S0, true, G, W, dt == nullptr, sres, npart))) return rc;
-  LAUNCH(k_dt_final, 1, W.smax, start_part(W), npart, 0, W.nflag, p->cfl, dt, W.dt, T.dt, W.stop,
-         (long long*)nullptr);
+  if ((rc = launch_start(st, p, user, T.S0, true, G, W, dt == nullptr, sres, nullptr, 0, npart)))
+    return rc;
+  const DtStep D = make_dt_step(p, W, npart, 0, dt, T.dt, nullptr);
   if (p->emf_compute == CTMHD_EMF_B25A) {
     LAUNCH((k_prim<double, kB25A>), nb, T.S0, G, W0, p->gamma, W.stop);
     if constexpr (first_step_stored(kB25A, RECON))
@@ -1166,7 +1167,7 @@ int record_box(const ctmhd_params* p_in, const ctmhd_box* box, double* const con
     if constexpr (first_step_stored(kFS18, RECON))
       LAUNCH((k_first_step<double, RECON, kFS18>), nb, G, W0, W.stop);
   }
-  if ((rc = launch_faces<double, RECON>(st, p, T.S0, G, W0, FP, 0, nullptr))) return rc;
+  if ((rc = launch_faces<double, RECON>(st, p, T.S0, G, W0, FP, 0, nullptr, &D))) return rc;
   if ((rc = launch_emf<double, RECON>(st, p, T.S0, G, W0, 0))) return rc;
   if ((rc = launch_update<double, 0>(st, nblocks(ninter), T.S0, T.S0, T.S1, G, W0, 0, U, nullptr,
                                      0)))

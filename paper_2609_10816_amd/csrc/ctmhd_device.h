@@ -145,16 +145,20 @@ __device__ __forceinline__ int pwrap(int s, int g, int n) {
   return q + g;
 }
 
-// Copy-back at the end of a call: a call whose step n was stopped (*stop =
-// n + 1) leaves S^n in the buffer that step n started from, which is the
-// caller's when nsteps - n is even.
-__global__ void k_restore(State user, State other, int elems, int nsteps, const int* stop) {
-  if (!*stop || !((nsteps - (*stop - 1)) & 1)) return;
-  for (int t = gidx(); t < elems; t += gridDim.x * blockDim.x) {
+// Copy-back at the end of a call, run by the last kernel of the call when it
+// was stopped: step n (*stop = n + 1) leaves S^n in the buffer that it started
+// from, which is the caller's when nsteps - n is even.
+struct Restore {
+  State user, other;
+  int elems, nsteps;  // nsteps 0: not the last kernel
+};
+__device__ __forceinline__ void restore_state(const Restore& R, int stop) {
+  if (R.nsteps == 0 || !((R.nsteps - (stop - 1)) & 1)) return;
+  for (int t = gidx(); t < R.elems; t += gridDim.x * blockDim.x) {
 #pragma unroll
-    for (int m = 0; m < 5; ++m) user.c[m][t] = other.c[m][t];
+    for (int m = 0; m < 5; ++m) R.user.c[m][t] = R.other.c[m][t];
 #pragma unroll
-    for (int a = 0; a < 3; ++a) user.b[a][t] = other.b[a][t];
+    for (int a = 0; a < 3; ++a) R.user.b[a][t] = R.other.b[a][t];
   }
 }
 
@@ -300,12 +304,17 @@ __device__ __forceinline__ double start_at(const State& src, const State& dst, b
 
 // One pass over the caller's state at the start of a call: ghost fill, the
 // copy into the buffer that the first step starts from, and the CFL maximum,
-// one partial value per workgroup (no counter needs clearing first).  Bound
+// one partial value per workgroup (no counter needs clearing first); also
+// clears the call's diagnostics and stop flag.  Bound
 // by memory: at 512^3 in FP64 it reads and writes the 8 fields once (4.2 ms;
 // separate ghost, CFL and copy passes took 5.5 ms; 128^3 65 against 109 us).
 __global__ void __launch_bounds__(kBlock)
     k_start(State src, State dst, int copy, Geom G, double gamma, double sres, int want_dt,
-            unsigned long long* part) {
+            unsigned long long* part, long long* diag, int ndiag, int* stop) {
+  if (blockIdx.x == 0) {
+    for (int q = threadIdx.x; q < ndiag; q += kBlock) diag[q] = 0;
+    if (threadIdx.x == 0) *stop = 0;
+  }
   double s = 0.0;
   for (int t = gidx(); t < G.elems; t += gridDim.x * blockDim.x) {
     const double v = start_at(src, dst, copy != 0, G, gamma, sres, want_dt != 0, t);
@@ -316,36 +325,43 @@ __global__ void __launch_bounds__(kBlock)
   if (threadIdx.x == 0) part[blockIdx.x] = m;
 }
 
-// dt of step n of a call, and the reset of the slots, the flag counters and
-// this step's diagnostics.  First step: the CFL maximum is that of the npart
-// partial values of k_start, and the stop flag is cleared.  Later steps:
+// dt of step n of a call (one workgroup), and the reset of the slots and the
+// flag counters.  First step: the CFL maximum is that of the npart partial
+// values of k_start, and the stop flag is cleared.  Later steps:
 // smax[0..kMaxSlots) holds it unless the previous step's second stage was
 // fixed up (nflag[2]), whose recomputed maximum is in smax[kMaxSlots..).
-__global__ void __launch_bounds__(kBlock)
-    k_dt_final(unsigned long long* smax, const unsigned long long* part, int npart, int n,
-               int* nflag, double cfl, const double* dt_fixed, double* dt, double* dt_out,
-               int* stop, long long* diag) {
+struct DtStep {
+  unsigned long long* smax;
+  const unsigned long long* part;
+  int npart, n;  // n < 0: none
+  int* nflag;
+  double cfl;
+  const double* dt_fixed;
+  double *dt, *dt_out;
+  int* stop;
+  long long* diag;  // this step's row, cleared by k_start
+};
+__device__ __forceinline__ void dt_step(const DtStep& D) {
   const int t = threadIdx.x;
-  const bool first = n == 0;
-  const unsigned long long* src = first ? part : (nflag[2] ? smax + kMaxSlots : smax);
-  const int cnt = first ? npart : kMaxSlots;
-  const int stopped = first ? 0 : *stop;
+  const bool first = D.n == 0;
+  const unsigned long long* src = first ? D.part : (D.nflag[2] ? D.smax + kMaxSlots : D.smax);
+  const int cnt = first ? D.npart : kMaxSlots;
+  const int stopped = first ? 0 : *D.stop;
   unsigned long long m = 0;
   for (int q = t; q < cnt; q += kBlock) m = src[q] > m ? src[q] : m;
   m = block_max_bits(__longlong_as_double((long long)m));
-  if (t < 2 * kMaxSlots) smax[t] = 0ull;
+  if (t < 2 * kMaxSlots) D.smax[t] = 0ull;
   if (t != 0) return;
-  nflag[0] = nflag[1] = nflag[2] = 0;
-  const double v = stopped ? 0.0 : (dt_fixed ? *dt_fixed : cfl / __longlong_as_double((long long)m));
-  const int halt = stopped ? stopped : ((!(v > 0.0) || !__builtin_isfinite(v)) ? n + 1 : 0);
-  if (diag) {
-    diag[0] = diag[1] = diag[2] = 0;
-    diag[3] = halt ? 1 : 0;
-  }
-  *stop = halt;
-  *dt = v;
-  if (dt_out) *dt_out = v;
+  D.nflag[0] = D.nflag[1] = D.nflag[2] = 0;
+  const double v =
+      stopped ? 0.0 : (D.dt_fixed ? *D.dt_fixed : D.cfl / __longlong_as_double((long long)m));
+  const int halt = stopped ? stopped : ((!(v > 0.0) || !__builtin_isfinite(v)) ? D.n + 1 : 0);
+  if (D.diag) D.diag[3] = halt ? 1 : 0;
+  *D.stop = halt;
+  *D.dt = v;
+  if (D.dt_out) *D.dt_out = v;
 }
+__global__ void __launch_bounds__(kBlock) k_dt_final(DtStep D) { dt_step(D); }
 
 // ---------------------------------------------------------------------------
 // Cell-centred fields for the two-step EMF schemes (B25a: ideal EMF; FS18:
@@ -910,6 +926,7 @@ struct FaceArgs {
   double gamma, eta;
   long long* diag;
   const int* stop;
+  DtStep D;  // the step's dt, formed by an extra workgroup (first stage of a step)
 };
 
 // The arguments are read where they are used, through the kernel argument
@@ -922,6 +939,12 @@ __global__ void __launch_bounds__(kBlock) k_faces(FaceArgs<T> byval) {
   (void)byval;
   const FaceArgs<T>& A =
       *(const FaceArgs<T>*)(const CTMHD_CONST FaceArgs<T>*)__builtin_amdgcn_kernarg_segment_ptr();
+  if ((int)blockIdx.x == A.FP.total_blocks) {
+    // nothing before the update needs dt, so it has no launch of its own; the
+    // faces of a step that this stops are solved in vain
+    dt_step(A.D);
+    return;
+  }
   if (*A.stop) return;
   int nfb = 0;
   faces_block<T, RECON, RIEMANN>(A.S, A.G, A.W, A.FP, blockIdx.x, A.stage, A.gamma, A.eta, nfb);
@@ -1120,9 +1143,9 @@ __device__ __forceinline__ T edge_emf(const State& S, const Geom& G, const Work<
   return eps;
 }
 
-// All three edge directions at the edge positions [g, g+n] on every axis
-// (an edge of direction c exists for s_c < g + n_c).
-template <typename T, int RECON, int EMF>
+// Edge directions [C0, C1) at the edge positions [g, g+n] on every axis (an
+// edge of direction c exists for s_c < g + n_c).
+template <typename T, int RECON, int EMF, int C0, int C1>
 __device__ __forceinline__ void emf_at(const State& S, const Geom& G, const Work<T>& W, int stage,
                                        double eta_d, int t) {
   const int L0 = G.n[0] + 1, L1 = G.n[1] + 1, L2 = G.n[2] + 1;
@@ -1130,15 +1153,31 @@ __device__ __forceinline__ void emf_at(const State& S, const Geom& G, const Work
   int s3[3] = {G.g + t % L0, G.g + (t / L0) % L1, G.g + t / (L0 * L1)};
   int s = s3[0] + G.st[1] * s3[1] + G.st[2] * s3[2];
 #pragma unroll
-  for (int c = 0; c < 3; ++c)
+  for (int c = C0; c < C1; ++c)
     if (s3[c] < G.g + G.n[c]) W.E[stage][c][s] = edge_emf<T, RECON, EMF>(S, G, W, s, c, eta_d);
 }
 
+// split > 0: one edge direction per thread, `split` workgroups per direction.
+// A small box leaves the chip idle while each thread forms its three edges one
+// after the other: 16^3 PPM Q26 12.0 -> SPLIT16 us per launch.
 template <typename T, int RECON, int EMF>
 __global__ void __launch_bounds__(kBlock)
-    k_emf3(State S, Geom G, Work<T> W, int stage, double eta_d, int band, const int* stop) {
+    k_emf3(State S, Geom G, Work<T> W, int stage, double eta_d, int band, int split,
+           const int* stop) {
   if (*stop) return;
-  emf_at<T, RECON, EMF>(S, G, W, stage, eta_d, xcd_band_tile(band) * kBlock + (int)threadIdx.x);
+  if (split > 0) {
+    const int c = (int)blockIdx.x / split;
+    const int t = ((int)blockIdx.x - c * split) * kBlock + (int)threadIdx.x;
+    if (c == 0)
+      emf_at<T, RECON, EMF, 0, 1>(S, G, W, stage, eta_d, t);
+    else if (c == 1)
+      emf_at<T, RECON, EMF, 1, 2>(S, G, W, stage, eta_d, t);
+    else
+      emf_at<T, RECON, EMF, 2, 3>(S, G, W, stage, eta_d, t);
+    return;
+  }
+  emf_at<T, RECON, EMF, 0, 3>(S, G, W, stage, eta_d,
+                              xcd_band_tile(band) * kBlock + (int)threadIdx.x);
 }
 
 // Q26 EMFs of one column of edge positions (x and y fixed, z in [z0, z1)),
@@ -1381,8 +1420,13 @@ __device__ __forceinline__ void update_item(const State& base, const State& half
 template <typename T, int stage, int fixup>
 __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 3)))
     k_update(State base, State half, State out, Geom G, Work<T> W, UpdateCfg U, long long* diag,
-             int band, const int* stop) {
-  if (*stop) return;
+             int band, Restore R, const int* stop) {
+  if (const int at_step = *stop) {
+    // the face pass of the step that stopped may have counted fallbacks
+    if (stage == 0 && !fixup && diag && gidx() == 0) diag[2] = 0;
+    restore_state(R, at_step);
+    return;
+  }
   if (!fixup) {
     update_item<T, stage, 0>(base, half, out, G, W, U, diag, xcd_band_tile(band), 1, W.smax,
                              blockIdx.x % kMaxSlots);
@@ -1828,7 +1872,7 @@ __device__ __forceinline__ void batch_item(const BatchArgs<T>& A, int b, int sta
     if (A.diag && nfb) atomicAdd((unsigned long long*)&A.diag[2], (unsigned long long)nfb);
   } else if constexpr (KIND == PH_E) {
     for (int s = 0; s < strips; ++s)
-      emf_at<T, RECON, EMF>(in, G, W, stage, A.eta, (tile * strips + s) * kBlock + threadIdx.x);
+      emf_at<T, RECON, EMF, 0, 3>(in, G, W, stage, A.eta, (tile * strips + s) * kBlock + threadIdx.x);
   } else if constexpr (KIND == PH_U || KIND == PH_X) {
     const State& oth = cl == 0 ? tb.sb : tb.su;
     UpdateCfg U;

@@ -211,11 +211,12 @@ inline int fix_blocks(int ninter) {
 // kernel of its own, so that none carries the registers of the others.
 template <typename T, int fixup>
 int launch_update(hipStream_t st, int blocks, State base, State half, State out, const Geom& G,
-                  const Work<T>& W, int stage, const UpdateCfg& U, long long* diag, int band) {
+                  const Work<T>& W, int stage, const UpdateCfg& U, long long* diag, int band,
+                  const Restore& R = Restore{}) {
   if (stage == 0)
-    LAUNCH((k_update<T, 0, fixup>), blocks, base, half, out, G, W, U, diag, band, W.stop);
+    LAUNCH((k_update<T, 0, fixup>), blocks, base, half, out, G, W, U, diag, band, R, W.stop);
   else
-    LAUNCH((k_update<T, 1, fixup>), blocks, base, half, out, G, W, U, diag, band, W.stop);
+    LAUNCH((k_update<T, 1, fixup>), blocks, base, half, out, G, W, U, diag, band, R, W.stop);
   return CTMHD_OK;
 }
 
@@ -229,10 +230,20 @@ unsigned long long* start_part(const Work<T>& W) {
 // layers into A (copy: another buffer) and npart partial CFL maxima.
 template <typename T>
 int launch_start(hipStream_t st, const ctmhd_params* p, State user, State A, bool copy,
-                 const Geom& G, const Work<T>& W, bool want_dt, double sres, int& npart) {
+                 const Geom& G, const Work<T>& W, bool want_dt, double sres, long long* diag,
+                 int ndiag, int& npart) {
   npart = fix_blocks(G.elems);
-  LAUNCH(k_start, npart, user, A, copy ? 1 : 0, G, p->gamma, sres, want_dt ? 1 : 0, start_part(W));
+  LAUNCH(k_start, npart, user, A, copy ? 1 : 0, G, p->gamma, sres, want_dt ? 1 : 0, start_part(W),
+         diag, ndiag, W.stop);
   return CTMHD_OK;
+}
+
+// The dt of step n of a call: given (dt_fixed) or from the CFL maximum.
+template <typename T>
+DtStep make_dt_step(const ctmhd_params* p, const Work<T>& W, int npart, int n,
+                    const double* dt_fixed, double* dt_out, long long* diag) {
+  return DtStep{W.smax, start_part(W), npart, n, W.nflag, p->cfl, dt_fixed, W.dt, dt_out, W.stop,
+                diag};
 }
 
 // Launch shape of the face pass when the tile knob leaves it open, from the
@@ -359,23 +370,25 @@ FacePlan box_face_plan(const ctmhd_params* p, const ctmhd_box& b, const Geom& G)
 
 template <typename T, int RECON>
 int launch_faces(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, const Work<T>& W,
-                 const FacePlan& FP, int stage, long long* diag) {
-  const FaceArgs<T> A{S, G, W, FP, stage, p->gamma, p->eta, diag, W.stop};
+                 const FacePlan& FP, int stage, long long* diag, const DtStep* dt = nullptr) {
+  const FaceArgs<T> A{S,    G,      W,    FP, stage, p->gamma, p->eta, diag,
+                      W.stop, dt ? *dt : DtStep{}};
+  const int blocks = FP.total_blocks + (dt ? 1 : 0);
   prof_begin(st);
   if constexpr (std::is_same<T, float>::value) {
     if (p->precision == CTMHD_FP32_R64) {
       if (p->riemann == CTMHD_RIEMANN_HLLD)
-        LAUNCH((k_faces<T, RECON, kHLLD64>), FP.total_blocks, A);
+        LAUNCH((k_faces<T, RECON, kHLLD64>), blocks, A);
       else
-        LAUNCH((k_faces<T, RECON, kLLF64>), FP.total_blocks, A);
+        LAUNCH((k_faces<T, RECON, kLLF64>), blocks, A);
       prof_end(st);
       return CTMHD_OK;
     }
   }
   if (p->riemann == CTMHD_RIEMANN_HLLD)
-    LAUNCH((k_faces<T, RECON, kHLLD>), FP.total_blocks, A);
+    LAUNCH((k_faces<T, RECON, kHLLD>), blocks, A);
   else
-    LAUNCH((k_faces<T, RECON, kLLF>), FP.total_blocks, A);
+    LAUNCH((k_faces<T, RECON, kLLF>), blocks, A);
   prof_end(st);
   return CTMHD_OK;
 }
@@ -385,6 +398,8 @@ int launch_faces(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, 
 // marches is a small part of the launch) and the shortest z chunk
 constexpr int kEmfTiles = 32768;
 constexpr int kEmfMinChunk = 8;
+// Workgroups of the per-edge kernel up to which it is split by direction
+constexpr int kEmfSplitBlocks = 512;
 
 // Workgroups of the z-marching edge kernel that the device holds at once (0 if
 // the runtime cannot say).  Queried once per instantiation.
@@ -408,6 +423,10 @@ int launch_emf(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, co
                int stage) {
   const int cnt = (G.n[0] + 1) * (G.n[1] + 1) * (G.n[2] + 1);
   const int band = xcd_band(p, (long long)(G.n[0] + 1) * (G.n[1] + 1), cnt);
+  // per-edge kernel: one edge direction per thread where the three together
+  // leave CUs without a workgroup
+  const int split = nblocks(cnt) <= kEmfSplitBlocks ? nblocks(cnt) : 0;
+  const int blocks = split ? 3 * split : nblocks(cnt);
   if (p->emf_compute == CTMHD_EMF_Q26) {
     // z marches: enough chunks for about kEmfTiles workgroups, at least
     // kEmfMinChunk positions each (the pipelines take 2r + 1 pushes to fill)
@@ -425,11 +444,11 @@ int launch_emf(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, co
     if (m == 2 || (m == 0 && 4LL * ctiles * nch >= 3LL * emf_march_resident<T, RECON>()))
       LAUNCH((k_emf_march<T, RECON>), ctiles * nch, S, G, W, stage, p->eta, ctiles, zc, W.stop);
     else
-      LAUNCH((k_emf3<T, RECON, kQ26>), nblocks(cnt), S, G, W, stage, p->eta, band, W.stop);
+      LAUNCH((k_emf3<T, RECON, kQ26>), blocks, S, G, W, stage, p->eta, band, split, W.stop);
   } else if (p->emf_compute == CTMHD_EMF_B25A)
-    LAUNCH((k_emf3<T, RECON, kB25A>), nblocks(cnt), S, G, W, stage, p->eta, band, W.stop);
+    LAUNCH((k_emf3<T, RECON, kB25A>), blocks, S, G, W, stage, p->eta, band, split, W.stop);
   else
-    LAUNCH((k_emf3<T, RECON, kFS18>), nblocks(cnt), S, G, W, stage, p->eta, band, W.stop);
+    LAUNCH((k_emf3<T, RECON, kFS18>), blocks, S, G, W, stage, p->eta, band, split, W.stop);
   return CTMHD_OK;
 }
 
