@@ -1159,7 +1159,7 @@ __device__ __forceinline__ void emf_at(const State& S, const Geom& G, const Work
 
 // split > 0: one edge direction per thread, `split` workgroups per direction.
 // A small box leaves the chip idle while each thread forms its three edges one
-// after the other: 16^3 PPM Q26 12.0 -> SPLIT16 us per launch.
+// after the other: 16^3 PPM Q26 12.0 -> 5.7 us per launch.
 template <typename T, int RECON, int EMF>
 __global__ void __launch_bounds__(kBlock)
     k_emf3(State S, Geom G, Work<T> W, int stage, double eta_d, int band, int split,
