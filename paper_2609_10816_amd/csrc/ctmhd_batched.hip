@@ -406,7 +406,8 @@ int phase_items(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, bool le
 constexpr int kSparseBlocks = 1024;
 
 template <typename T, int RECON, int RIEMANN, int EMF>
-int launch_bphase(hipStream_t st, int kind, long long items, const BatchArgs<T>& A, int q) {
+int launch_bphase(hipStream_t st, int kind, int xarg, long long items, const BatchArgs<T>& A,
+                  int q) {
   if (items <= 0) return CTMHD_OK;
   const unsigned grid = (unsigned)items;
   const unsigned few = items < kSparseBlocks ? (unsigned)items : (unsigned)kSparseBlocks;
@@ -423,7 +424,12 @@ int launch_bphase(hipStream_t st, int kind, long long items, const BatchArgs<T>&
       // the CFL maxima of independent boxes are formed by PH_WRAP
       if (A.level) LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_DT>), grid, A, q);
       break;
-    case PH_XCHG: LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_XCHG>), grid, A, q); break;
+    case PH_XCHG:
+      if (xarg & XG_IF_FIXUP)  // usually nothing was flagged
+        LAUNCH((k_bsparse<T, kQ26, PH_XCHG>), few, A, q);
+      else
+        LAUNCH((k_bphase<T, kPC, kHLLD, kQ26, PH_XCHG>), grid, A, q);
+      break;
     default: LAUNCH((k_bsparse<T, kQ26, PH_COPY>), few, A, q); break;
   }
   return CTMHD_OK;
@@ -469,7 +475,7 @@ int batched_run(const ctmhd_params* p, int nbox, const ctmhd_box* boxes, const L
     }
     for (int q = range[l][0]; q < range[l][1]; ++q) {
       if (kind[q] == PH_F) prof_begin(st);
-      int r = launch_bphase<T, RECON, RIEMANN, EMF>(st, kind[q], items[q], A, q);
+      int r = launch_bphase<T, RECON, RIEMANN, EMF>(st, kind[q], xarg[q], items[q], A, q);
       if (r) return r;
       if (kind[q] == PH_F) prof_end(st);
     }

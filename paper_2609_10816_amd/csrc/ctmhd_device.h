@@ -1900,7 +1900,6 @@ __device__ __forceinline__ void batch_item(const BatchArgs<T>& A, int b, int sta
     }
     if (A.want_dt) block_max_to_slots(sig, W.smax, 0);
   } else if constexpr (KIND == PH_XCHG) {
-    if ((xa & XG_IF_FIXUP) && !W.nflag[stage]) return;
     const int tg = xa & XG_TARGET;
     // packed (unshifted) arrays: the owner of a ghost block is another box;
     // the caller's state goes to the buffer that the first step starts from
@@ -2012,7 +2011,7 @@ __global__ void __launch_bounds__(kBlock) k_batch(BatchArgs<T> A) {
       case PH_O: if (tab_nflag(A, b)[stage]) batch_item<T, RECON, RIEMANN, EMF, PH_O>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
       case PH_WRAP: batch_item<T, RECON, RIEMANN, EMF, PH_WRAP>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
       case PH_DT: batch_item<T, RECON, RIEMANN, EMF, PH_DT>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
-      case PH_XCHG: batch_item<T, RECON, RIEMANN, EMF, PH_XCHG>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
+      case PH_XCHG: if (!(P->xarg[p] & XG_IF_FIXUP) || tab_nflag(A, b)[stage]) batch_item<T, RECON, RIEMANN, EMF, PH_XCHG>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
       default: batch_item<T, RECON, RIEMANN, EMF, PH_COPY>(A, b, stage, tile, strips, cl, P->xarg[p]); break;
     }
     signal_count(A.done + (long long)p * nbox + b);
@@ -2049,8 +2048,8 @@ __global__ void __launch_bounds__(kBlock) k_bphase(BatchArgs<T> A, int p) {
                                            P->xarg[p]);
 }
 
-// A phase that most boxes have no work in (the first-order pass, the fix-up
-// and the copy-back of a stopped call): a grid of a few workgroups per CU
+// A phase that most boxes have no work in (the first-order pass, the fix-up,
+// a level's exchange after it and the copy-back of a stopped call): a grid of a few workgroups per CU
 // looks for the boxes that have some, 256 at a time, and shares their tiles
 // out.  With one workgroup per tile of every box, four such launches that
 // found nothing took 1.7 ms of a step of 2000 boxes (2 x 430 + 2 x 370 us).
