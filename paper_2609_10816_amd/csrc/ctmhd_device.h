@@ -668,12 +668,13 @@ __device__ __forceinline__ void face_nb(const State& S, const Geom& G, int s, in
 }
 
 // Value of the neighbouring lane (l - 1 for lane_prev, l + 1 for lane_next)
-// by a DPP whole-wavefront shift, a VALU move; lane 0 (63) receives 0.
+// by a DPP whole-wavefront shift, a VALU move; lane 0 (63) receives 0 by the
+// bound control, so that no register has to be cleared for it first.
 __device__ __forceinline__ int dpp_prev(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x138, 0xf, 0xf, false);  // wave_shr:1
+  return __builtin_amdgcn_mov_dpp(v, 0x138, 0xf, 0xf, true);  // wave_shr:1
 }
 __device__ __forceinline__ int dpp_next(int v) {
-  return __builtin_amdgcn_update_dpp(0, v, 0x130, 0xf, 0xf, false);  // wave_shl:1
+  return __builtin_amdgcn_mov_dpp(v, 0x130, 0xf, 0xf, true);  // wave_shl:1
 }
 __device__ __forceinline__ double lane_prev(double v) {
   return __hiloint2double(dpp_prev(__double2hiint(v)), dpp_prev(__double2loint(v)));
@@ -1180,71 +1181,185 @@ __global__ void __launch_bounds__(kBlock)
                               xcd_band_tile(band) * kBlock + (int)threadIdx.x);
 }
 
-// Q26 EMFs of one column of edge positions (x and y fixed, z in [z0, z1)),
-// marching up z.  The four reconstructions along z -- B_y and u*_y at the x
-// edges, B_x and u*_x at the y edges -- run as streams that take one cell
-// and complete one per position, as in the face marches, instead of loading
-// and limiting six cells per edge; the other reconstructions, the wave speeds
-// and eta j are those of edge_emf.  The streamed values are the same
-// arithmetic on the same cells, so the EMFs equal emf_at's.
+// The same 1D interface values for a row of cells across a wavefront: q is the
+// lane's cell, lo / hi the values on the lower and upper side of the interface
+// below it (valid r + 1 lanes from the lower and r from the upper end).
+template <int RECON, typename T>
+__device__ __forceinline__ void iface_lanes(T q, T& lo, T& hi) {
+  T qp;
+  recon_lanes<RECON>(q, hi, qp);
+  lo = lane_prev(qp);
+}
+
+// y interface values at s of an array whose own value is known (q0, cast to
+// the stencil type); below: the element at s - sy.
+template <int RECON, typename T, typename U>
+__device__ __forceinline__ void iface_y(const U* A, int s, int sy, U q0, U& below, T& lo, T& hi) {
+  T q[6];
+  below = at(A, s - sy);
+#pragma unroll
+  for (int m = 0; m < 6; ++m)
+    q[m] = !stencil_uses<RECON>(m) ? T(0)
+           : m == 3 ? (T)q0 : m == 2 ? (T)below : (T)at(A, s + (m - 3) * sy);
+  recon_iface<RECON>(q, lo, hi);
+}
+
+// Q26 EMFs of a row of edge columns per wavefront (64 consecutive x, y fixed),
+// marching up z over [z0, z1).  Each of the twelve reconstructions of a
+// position takes the cheapest form its axis allows, all of them the arithmetic
+// of edge_emf on the same cells:
+//   along z (B_y, u*_y at the x edges, B_x, u*_x at the y edges) streams that
+//     take one cell and complete one per position, as in the face marches;
+//   along x (B_y, u*_y at the z edges, B_z, u*_z at the y edges) one cell per
+//     lane, neighbours by whole-wavefront shifts, as in the x faces: 59 of 64
+//     lanes resolve positions with PPM;
+//   along y (B_x, u*_x at the z edges, B_z, u*_z at the x edges) six loads each,
+//     their own value from the stream or shared.
+// Edge speeds and eta j take the x neighbours from the lane below and the z
+// neighbours from the position before.  Against twelve six-point forms with the
+// z ones streamed (1168 VALU instructions and 64 loads per position in the FP64
+// PPM kernel, now 1040 and 38): 512^3 FP64 PPM 7.53 -> 6.40 ms per launch, 256^3
+// FP64 PLM 767 -> 565 us, 256^3 FP32 604 -> 533, 128^3 FP64 146 -> 125.
 template <typename T, int RECON>
 __device__ __forceinline__ void emf_march_q26(const State& S, const Geom& G, const Work<T>& W,
-                                              int stage, double eta_d, int col, int z0, int z1) {
+                                              int stage, double eta_d, int item, int z0, int z1) {
   constexpr int r = recon_halfwidth(RECON);
-  const int L0 = G.n[0] + 1;
-  const int x = G.g + col % L0, y = G.g + col / L0;
+  const int lane = threadIdx.x & 63;
   const int sy = G.st[1], sz = G.st[2];
-  const bool xe = x < G.g + G.n[0], ye = y < G.g + G.n[1];  // x / y edges exist here
+  // this lane's column: cell xi of the extended row yi (rows of n0 + 1 edge
+  // positions and their halo, laid end to end)
+  const int xw = G.n[0] + 2 * r + 2;
+  const int e = item * (63 - 2 * r) + lane;
+  int yi = e / xw;
+  const int xi = e - yi * xw;
+  const bool mine = lane >= r + 1 && lane <= 63 - r && xi >= r + 1 && xi <= r + 1 + G.n[0] &&
+                    yi <= G.n[1];
+  if (yi > G.n[1]) yi = G.n[1];
+  const int x = G.g - (r + 1) + xi, y = G.g + yi;
+  const bool xe = mine && x < G.g + G.n[0], ye = mine && yi < G.n[1];  // x / y edges here
   const int base = x + sy * y;
   ReconStream<RECON, T> rs[4];  // B_y, u*_y (x edges), B_x, u*_x (y edges)
   T lo[4];                      // upper values of the cell below the next position
+  // the position below: speeds of the x and y faces, b_x and b_y
+  T apx0, amx0, apy0, amy0;
+  double bx0, by0;
+  {
+    const int s = base + (z0 - 1) * sz;
+    apx0 = at(W.ap[0], s);
+    amx0 = at(W.am[0], s);
+    apy0 = at(W.ap[1], s);
+    amy0 = at(W.am[1], s);
+    bx0 = at(S.b[0], s);
+    by0 = at(S.b[1], s);
+  }
   // cells z0-1-r .. z1-1+r; the pushes before cell z0-1+r only fill the
   // pipelines (their streams' cells lie in the ghost layers)
   for (int q = z0 - 1 - r; q <= z1 - 1 + r; ++q) {
     const int sq = base + q * sz;
-    const T v[4] = {(T)S.b[1][sq], W.us[1][sq], (T)S.b[0][sq], W.us[0][sq]};
+    const T v[4] = {(T)at(S.b[1], sq), at(W.us[1], sq), (T)at(S.b[0], sq), at(W.us[0], sq)};
+    T own[4];  // the values of the cell completed by this push
     T qm[4], qp[4];
 #pragma unroll
-    for (int k = 0; k < 4; ++k) rs[k].push(v[k], qm[k], qp[k]);
-    const int z = q - r;  // the cell completed by this push
+    for (int k = 0; k < 4; ++k) {
+      own[k] = RECON == kPPM ? rs[k].q2 : RECON == kPC ? v[k] : rs[k].q1;
+      rs[k].push(v[k], qm[k], qp[k]);
+    }
+    const int z = q - r;
     if (z >= z0) {
       const int s = base + z * sz;
-      if (xe) {  // a = y (streamed along z), b = z (along y)
-        T bbL, bbR, ubL, ubR;
-        iface_along_d<RECON>(S.b[2], s, sy, bbL, bbR);
-        iface_along<RECON>(W.us[2], s, sy, ubL, ubR);
-        W.E[stage][0][s] =
-            q26_edge<T>(S, G, W, s, 0, lo[0], qm[0], bbL, bbR, lo[1], qm[1], ubL, ubR, eta_d);
+      const double bz = at(S.b[2], s);
+      const T uz = at(W.us[2], s);
+      // own face fields in double (the streams hold the stencil type)
+      double bx, by;
+      if constexpr (std::is_same<T, double>::value) {
+        by = own[0];
+        bx = own[2];
+      } else {
+        by = at(S.b[1], s);
+        bx = at(S.b[0], s);
       }
-      if (ye) {  // a = z (along x), b = x (streamed along z)
-        T baB, baT, uaB, uaT;
-        iface_along_d<RECON>(S.b[2], s, 1, baB, baT);
-        iface_along<RECON>(W.us[2], s, 1, uaB, uaT);
-        W.E[stage][1][s] =
-            q26_edge<T>(S, G, W, s, 1, baB, baT, lo[2], qm[2], uaB, uaT, lo[3], qm[3], eta_d);
+      double bx_y, bz_y;  // b_x and b_z at s - sy
+      T u_y;
+      const T apx = at(W.ap[0], s), amx = at(W.am[0], s);
+      const T apy = at(W.ap[1], s), amy = at(W.am[1], s);
+      const T apz = at(W.ap[2], s), amz = at(W.am[2], s);
+      // edge direction c with a = c+1, b = c+2
+      T e0, e1, e2;
+      {
+        T zyL, zyR, uzyL, uzyR;
+        iface_y<RECON>(S.b[2], s, sy, bz, bz_y, zyL, zyR);
+        iface_y<RECON>(W.us[2], s, sy, uz, u_y, uzyL, uzyR);
+        const T apz_y = at(W.ap[2], s - sy), amz_y = at(W.am[2], s - sy);
+        e0 = q26_ld04(lo[1], qm[1], uzyL, uzyR, lo[0], qm[0], zyL, zyR, tmax(apy0, apy),
+                      tmax(amy0, amy), tmax(apz_y, apz), tmax(amz_y, amz));
       }
-      if (z < G.g + G.n[2]) W.E[stage][2][s] = edge_emf<T, RECON, kQ26>(S, G, W, s, 2, eta_d);
+      {
+        T zxL, zxR, uzxL, uzxR;
+        iface_lanes<RECON>((T)bz, zxL, zxR);
+        iface_lanes<RECON>(uz, uzxL, uzxR);
+        const T apz_x = lane_prev(apz), amz_x = lane_prev(amz);
+        e1 = q26_ld04(uzxL, uzxR, lo[3], qm[3], zxL, zxR, lo[2], qm[2], tmax(apz_x, apz),
+                      tmax(amz_x, amz), tmax(apx0, apx), tmax(amx0, amx));
+      }
+      {
+        T xyL, xyR, uxyL, uxyR, yxL, yxR, uyxL, uyxR;
+        iface_y<RECON>(S.b[0], s, sy, bx, bx_y, xyL, xyR);
+        iface_y<RECON>(W.us[0], s, sy, own[3], u_y, uxyL, uxyR);
+        iface_lanes<RECON>(own[0], yxL, yxR);
+        iface_lanes<RECON>(own[1], uyxL, uyxR);
+        const T apx_y = at(W.ap[0], s - sy), amx_y = at(W.am[0], s - sy);
+        const T apy_x = lane_prev(apy), amy_x = lane_prev(amy);
+        e2 = q26_ld04(uxyL, uxyR, uyxL, uyxR, xyL, xyR, yxL, yxR, tmax(apx_y, apx),
+                      tmax(amx_y, amx), tmax(apy_x, apy), tmax(amy_x, amy));
+      }
+      if (eta_d > 0.0) {  // eta_j
+        const T eta = (T)eta_d;
+        const double by_x = lane_prev(by), bz_x = lane_prev(bz);
+        const double j0 = (bz - bz_y) * G.idx[1] - (by - by0) * G.idx[2];
+        const double j1 = (bx - bx0) * G.idx[2] - (bz - bz_x) * G.idx[0];
+        const double j2 = (by - by_x) * G.idx[0] - (bx - bx_y) * G.idx[1];
+        e0 += eta * (T)j0;
+        e1 += eta * (T)j1;
+        e2 += eta * (T)j2;
+      }
+      if (xe) at(W.E[stage][0], s) = e0;
+      if (ye) at(W.E[stage][1], s) = e1;
+      if (mine && z < G.g + G.n[2]) at(W.E[stage][2], s) = e2;
+      apx0 = apx;
+      amx0 = amx;
+      apy0 = apy;
+      amy0 = amy;
+      bx0 = bx;
+      by0 = by;
     }
 #pragma unroll
     for (int k = 0; k < 4; ++k) lo[k] = qp[k];
   }
 }
 
-// Q26 edge pass as z marches: workgroup tile = chunk * ctiles + column tile
-// (columns x fastest, kBlock per tile), z chunks of zc positions.  Through
-// xcd_tile each XCD takes a contiguous run of tiles: a slab of z chunks over
-// a band of rows, so the y neighbours a column reads share its XCD's L2.
+// Wavefront items of the z-marching Q26 edge pass.
+__host__ __device__ inline int emf_march_items(const Geom& G, int r) {
+  const int len = (G.n[0] + 2 * r + 2) * (G.n[1] + 1);
+  return (len - 2 * r - 1 + 62 - 2 * r) / (63 - 2 * r);
+}
+
+// Q26 edge pass as z marches: workgroup tile = chunk * ctiles + tile of four
+// items, z chunks of zc positions.  Through xcd_tile each XCD takes a contiguous
+// run of tiles: a slab of z chunks over a band of rows, so the y neighbours a
+// column reads share its XCD's L2.
+// (Three wavefronts per SIMD: 166 registers.  At four the PPM kernel spills and
+// takes twice as long.)
 template <typename T, int RECON>
-__global__ void __launch_bounds__(kBlock)
+__global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3)))
     k_emf_march(State S, Geom G, Work<T> W, int stage, double eta_d, int ctiles, int zc,
                 const int* stop) {
   if (*stop) return;
   const int tile = xcd_tile();
-  const int col = (tile % ctiles) * kBlock + (int)threadIdx.x;
-  if (col >= (G.n[0] + 1) * (G.n[1] + 1)) return;
+  const int item = (tile % ctiles) * (kBlock / 64) + (int)(threadIdx.x >> 6);
+  if (item >= emf_march_items(G, recon_halfwidth(RECON))) return;  // whole wavefronts
   const int z0 = G.g + (tile / ctiles) * zc;
   const int zend = G.g + G.n[2] + 1;
-  emf_march_q26<T, RECON>(S, G, W, stage, eta_d, col, z0, z0 + zc < zend ? z0 + zc : zend);
+  emf_march_q26<T, RECON>(S, G, W, stage, eta_d, item, z0, z0 + zc < zend ? z0 + zc : zend);
 }
 
 // ---------------------------------------------------------------------------

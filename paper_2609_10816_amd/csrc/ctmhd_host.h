@@ -396,11 +396,10 @@ int launch_faces(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, 
   return CTMHD_OK;
 }
 
-// Q26 edge pass: the number of workgroups aimed at (many times the number
-// that run at once, so that the last, partial round of these equally long
-// marches is a small part of the launch) and the shortest z chunk
+// Q26 edge pass as z marches: the most workgroups (so that the search below is
+// short) and the shortest z chunk
 constexpr int kEmfTiles = 32768;
-constexpr int kEmfMinChunk = 8;
+constexpr int kEmfMinChunk = 5;
 // Workgroups of the per-edge kernel up to which it is split by direction
 constexpr int kEmfSplitBlocks = 512;
 
@@ -431,13 +430,22 @@ int launch_emf(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, co
   const int split = nblocks(cnt) <= kEmfSplitBlocks ? nblocks(cnt) : 0;
   const int blocks = split ? 3 * split : nblocks(cnt);
   if (p->emf_compute == CTMHD_EMF_Q26) {
-    // z marches: enough chunks for about kEmfTiles workgroups, at least
-    // kEmfMinChunk positions each (the pipelines take 2r + 1 pushes to fill)
-    const int ctiles = nblocks((G.n[0] + 1) * (G.n[1] + 1));
-    const int L2 = G.n[2] + 1;
-    int nch = (kEmfTiles + ctiles - 1) / ctiles;
-    if (nch > L2 / kEmfMinChunk) nch = L2 / kEmfMinChunk;
-    if (nch < 1) nch = 1;
+    // z marches: the number of chunks with the smallest number of rounds of the
+    // chip times the length of a march (its positions and the filling of its
+    // pipelines, about a position and a half)
+    const int ctiles = (emf_march_items(G, recon_halfwidth(RECON)) + kBlock / 64 - 1) / (kBlock / 64);
+    const int L2 = G.n[2] + 1, res = emf_march_resident<T, RECON>();
+    int nch = 1;
+    double best = 0.0;
+    for (int k = 1; k <= L2 / kEmfMinChunk && k <= kEmfTiles / ctiles + 1; ++k) {
+      const int len = (L2 + k - 1) / k;
+      const double rounds = res > 0 ? (double)((ctiles * ((L2 + len - 1) / len) + res - 1) / res) : 1.0;
+      const double cost = rounds * (len + 1.5);
+      if (k == 1 || cost < best) {
+        best = cost;
+        nch = k;
+      }
+    }
     const int zc = (L2 + nch - 1) / nch;
     nch = (L2 + zc - 1) / zc;
     // automatic: a small box gives the marches less than about one round of
