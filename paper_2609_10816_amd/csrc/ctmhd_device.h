@@ -1420,6 +1420,91 @@ struct UpdateCfg {
   int flag_storage;  // 1: flags indexed by storage position (a level of boxes)
 };
 
+// The new conserved values c and lower face fields bl of the cell at s and,
+// with need_state, its upper face fields bu, recomputed with the same arithmetic
+// as the neighbour that owns them (for the flags and the CFL signal).  fix: the
+// form after a first-order replacement.
+template <typename T, int stage, int fix>
+__device__ __forceinline__ void cell_form(const State& base, const State& half, const Geom& G,
+                                          const Work<T>& W, bool need_state, int s, double dt,
+                                          double c[5], double bl[3], double bu[3]) {
+#pragma clang fp contract(off)
+#pragma unroll
+  for (int m = 0; m < 5; ++m) {
+    if (stage == 0)
+      c[m] = base.c[m][s] + dcons(G, W, 0, s, m, dt);
+    else if (!fix)
+      c[m] = 0.5 * (base.c[m][s] + half.c[m][s] + dcons(G, W, 1, s, m, dt));
+    else
+      c[m] = base.c[m][s] + 0.5 * (dcons(G, W, 0, s, m, dt) + dcons(G, W, 1, s, m, dt));
+  }
+#pragma unroll
+  for (int a = 0; a < 3; ++a) bl[a] = new_face(base, half, G, W, stage, fix, s, a, dt);
+  if (need_state) {
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+      bu[a] = new_face(base, half, G, W, stage, fix, s + gstride(G, a), a, dt);
+  }
+}
+
+// The fix-up touches only the cells that the first-order values can reach: those
+// with a flagged cell among their 27 neighbours (faces and edges are shared by
+// no others).  The main update of a stage leaves, in the speed arrays that only
+// the face and edge passes before it use, the list of its flagged cells and a
+// word per item (256 strips cells): non-zero, in the second stage the item's
+// CFL maximum.  The first-order pass works through the list and clears the
+// words of the items it reaches; the fix-up skips the others.  On the 128^3
+// Mach-5 box with some cells flagged (FP64 PPM Q26), first-order pass and fix-up
+// of the first / second stage take 26 + 19 / 42 us; 57 + 144 / 262 us when both
+// went over the whole box.  In a level, whose flags come from the neighbouring
+// boxes too, both go over the whole boxes, for the same cells.
+template <typename T>
+__device__ __forceinline__ int* flag_list(const Work<T>& W) {
+  return (int*)W.am[0];
+}
+template <typename T>
+__device__ __forceinline__ unsigned* item_word(const Work<T>& W, int item) {
+  return (unsigned*)W.ap[0] + 2 * (size_t)item;
+}
+// Whether the first-order pass works through the list (few flagged cells).
+__device__ __forceinline__ bool few_flagged(const Geom& G, int nflag) {
+  return 27LL * nflag < (long long)G.n[0] * G.n[1] * G.n[2];
+}
+
+__device__ __forceinline__ int interior_id(const Geom& G, int s0, int s1, int s2) {
+  int i = (s0 - G.g) % G.n[0];
+  if (i < 0) i += G.n[0];
+  int j = (s1 - G.g) % G.n[1];
+  if (j < 0) j += G.n[1];
+  int k = (s2 - G.g) % G.n[2];
+  if (k < 0) k += G.n[2];
+  return i + G.n[0] * (j + G.n[1] * k);
+}
+
+// Flag of the cell at storage coordinates p3: periodic box (interior flags,
+// wrapped) or a level of boxes (flags at every storage position, the ghost
+// layers filled from the neighbouring boxes).
+template <typename T>
+__device__ __forceinline__ uint8_t flag_of(const Geom& G, const Work<T>& W, bool lvl,
+                                           const int p3[3]) {
+  if (lvl) return W.flag[p3[0] + G.st[1] * p3[1] + G.st[2] * p3[2]];
+  return W.flag[interior_id(G, p3[0], p3[1], p3[2])];
+}
+
+// Whether a cell (storage coordinates) or one of its neighbours is flagged.
+template <typename T>
+__device__ __forceinline__ bool near_flagged(const Geom& G, const Work<T>& W, bool lvl,
+                                             const int s3[3]) {
+  int f = 0;
+  for (int dz = -1; dz <= 1; ++dz)
+    for (int dy = -1; dy <= 1; ++dy)
+      for (int dx = -1; dx <= 1; ++dx) {
+        const int p3[3] = {s3[0] + dx, s3[1] + dy, s3[2] + dz};
+        f |= flag_of(G, W, lvl, p3);
+      }
+  return f != 0;
+}
+
 // fixup = 0: main update (flags, and for stage 1 the CFL maximum into slot 0)
 // fixup = 1: after first-order replacement; runs only if this stage flagged
 //            cells; stage 1 recomputes the CFL maximum into slot 1.
@@ -1437,6 +1522,23 @@ __device__ __forceinline__ void update_item(const State& base, const State& half
   const int ninter = G.n[0] * G.n[1] * G.n[2];
   const double dt = *W.dt;
   double sigmax = 0.0;
+  const bool words = U.fofc && !U.flag_storage;  // a level has none
+  // held in vector registers: as scalars the address and the condition no
+  // longer fit beside the other pointers, and the compiler then spills them and
+  // drains the loads as it goes (stage 2 at 256^3 FP32: 1103 us, like this 924)
+  unsigned* word = (words && threadIdx.x == 0) ? item_word(W, vb) : nullptr;
+  asm volatile("" : "+v"(word));
+  if (fixup && words) {
+    const unsigned* w = item_word(W, vb);
+    const unsigned long long m = w[0] | ((unsigned long long)w[1] << 32);
+    if (m != 0) {  // no first-order value reaches this item
+      if (stage == 1 && threadIdx.x == 0) {
+        W.nflag[2] = 1;
+        atomicMax(&slots[slot], m);
+      }
+      return;
+    }
+  }
   for (int strip = 0; strip < strips; ++strip) {
   const int t = (vb * strips + strip) * kBlock + (int)threadIdx.x;
   const bool live = t < ninter;
@@ -1449,27 +1551,24 @@ __device__ __forceinline__ void update_item(const State& base, const State& half
     const int k0 = q / G.n[1];
     const int p3[3] = {i0, j0, k0};
     const int s = (i0 + G.g) + G.st[1] * (j0 + G.g) + G.st[2] * (k0 + G.g);
-    double c[5], bl[3];
-#pragma unroll
-    for (int m = 0; m < 5; ++m) {
-      if (stage == 0)
-        c[m] = base.c[m][s] + dcons(G, W, 0, s, m, dt);
-      else if (!fixup)
-        c[m] = 0.5 * (base.c[m][s] + half.c[m][s] + dcons(G, W, 1, s, m, dt));
-      else
-        c[m] = base.c[m][s] + 0.5 * (dcons(G, W, 0, s, m, dt) + dcons(G, W, 1, s, m, dt));
-    }
-#pragma unroll
-    for (int a = 0; a < 3; ++a) bl[a] = new_face(base, half, G, W, stage, fixup, s, a, dt);
-    // upper faces of this cell, recomputed with the same arithmetic as the
-    // neighbour that owns them (for the flags and the CFL signal); formed
-    // before the stores below, which the compiler cannot move loads across
     const bool need_state = (U.fofc && !fixup) || stage == 1;
+    double c[5], bl[3];
+    // (formed before the stores below, which the compiler cannot move loads across)
     double bu[3] = {0.0, 0.0, 0.0};
-    if (need_state) {
-#pragma unroll
-      for (int a = 0; a < 3; ++a)
-        bu[a] = new_face(base, half, G, W, stage, fixup, s + gstride(G, a), a, dt);
+    // fix-up: the other cells of an item keep their state; the second stage
+    // forms their CFL signal again
+    bool write = true;
+    if constexpr (fixup) {
+      const int g3[3] = {i0 + G.g, j0 + G.g, k0 + G.g};
+      write = near_flagged(G, W, U.flag_storage != 0, g3);
+    }
+    if constexpr (!fixup) {
+      cell_form<T, stage, 0>(base, half, G, W, need_state, s, dt, c, bl, bu);
+    } else {
+      if (write)
+        cell_form<T, stage, 1>(base, half, G, W, need_state, s, dt, c, bl, bu);
+      else if (stage == 1)
+        cell_form<T, stage, 0>(base, half, G, W, need_state, s, dt, c, bl, bu);
     }
     // periodic images: every storage position congruent to this cell
     int mlo[3], mhi[3];
@@ -1479,6 +1578,7 @@ __device__ __forceinline__ void update_item(const State& base, const State& half
       mlo[d] = -(pos / G.n[d]);
       mhi[d] = (G.N[d] - 1 - pos) / G.n[d];
     }
+    if (!write) mhi[2] = mlo[2] - 1;
     for (int mz = mlo[2]; mz <= mhi[2]; ++mz)
       for (int my = mlo[1]; my <= mhi[1]; ++my)
         for (int mx = mlo[0]; mx <= mhi[0]; ++mx) {
@@ -1514,17 +1614,29 @@ __device__ __forceinline__ void update_item(const State& base, const State& half
   }
   if (U.fofc && !fixup) {
     unsigned long long m = __ballot(bad);
-    if ((threadIdx.x & 63) == 0 && m) {
-      int cnt = __popcll(m);
-      atomicAdd(&W.nflag[stage], cnt);
-      if (diag) atomicAdd((unsigned long long*)&diag[stage], (unsigned long long)cnt);
+    if (m) {
+      const int lane = threadIdx.x & 63;
+      int first = 0;
+      if (lane == 0) {
+        int cnt = __popcll(m);
+        first = atomicAdd(&W.nflag[stage], cnt);
+        if (diag) atomicAdd((unsigned long long*)&diag[stage], (unsigned long long)cnt);
+      }
+      first = __shfl(first, 0, 64);
+      if (words && bad) flag_list(W)[first + __popcll(m & ((1ull << lane) - 1))] = t;
     }
   }
   sigmax = (sig > sigmax || sig != sig) ? sig : sigmax;
   }
+  unsigned long long most = 1;
   if (stage == 1) {
     if (fixup && threadIdx.x == 0) W.nflag[2] = 1;
-    block_max_to_slots(sigmax, slots, slot);
+    most = block_max_bits(sigmax);
+    if (threadIdx.x == 0) atomicMax(&slots[slot], most);
+  }
+  if (!fixup && word) {
+    word[0] = (unsigned)most;
+    word[1] = (unsigned)(most >> 32);
   }
 }
 
@@ -1560,16 +1672,6 @@ __global__ void __launch_bounds__(kBlock) __attribute__((amdgpu_waves_per_eu(3, 
 // First-order flux correction (Sec. 2.5): faces touching a flagged cell take
 // the PC + LLF flux of S^n, edges touching one the first-order EMF of S^n.
 // ---------------------------------------------------------------------------
-__device__ __forceinline__ int interior_id(const Geom& G, int s0, int s1, int s2) {
-  int i = (s0 - G.g) % G.n[0];
-  if (i < 0) i += G.n[0];
-  int j = (s1 - G.g) % G.n[1];
-  if (j < 0) j += G.n[1];
-  int k = (s2 - G.g) % G.n[2];
-  if (k < 0) k += G.n[2];
-  return i + G.n[0] * (j + G.n[1] * k);
-}
-
 // First-order (PC + LLF) flux at the x_a face s; returns s_LLF and u*.
 template <typename T>
 __device__ __forceinline__ T fo_face(const State& S, const Geom& G, int s, int a, double gamma_d,
@@ -1599,16 +1701,6 @@ __device__ __forceinline__ T fo_corner_cell(const State& Sn, const Geom& G, int 
   cell_prim(Sn, G, s, gamma, rho, u, p, bc);
   if (EMF == kB25A) return -(T)u[a] * (T)bc[b] + (T)u[b] * (T)bc[a];
   return -(T)u[a] * bbX + (T)u[b] * baY;  // FS18 with PC: cell velocity, edge field
-}
-
-// Flag of the cell at storage coordinates p3: periodic box (interior flags,
-// wrapped) or a level of boxes (flags at every storage position, the ghost
-// layers filled from the neighbouring boxes).
-template <typename T>
-__device__ __forceinline__ uint8_t flag_of(const Geom& G, const Work<T>& W, bool lvl,
-                                           const int p3[3]) {
-  if (lvl) return W.flag[p3[0] + G.st[1] * p3[1] + G.st[2] * p3[2]];
-  return W.flag[interior_id(G, p3[0], p3[1], p3[2])];
 }
 
 // One thread per cell position s: its three lower faces and the three edges
@@ -1695,6 +1787,28 @@ __device__ __forceinline__ void fo_at(const State& Sn, const Geom& G, const Work
   }
 }
 
+// Work unit q of the first-order pass of a periodic box (item: 256 strips
+// cells), of fo_units: neighbour q % 27 of flagged cell q / 27, or cell q when
+// many are flagged.  Two units may be the same cell; both write its values.
+template <typename T>
+__device__ __forceinline__ int fo_units(const Geom& G, const Work<T>& W, int stage) {
+  const int nf = W.nflag[stage];
+  return few_flagged(G, nf) ? 27 * nf : G.n[0] * G.n[1] * G.n[2];
+}
+template <typename T, int EMF>
+__device__ __forceinline__ void fo_unit(const State& Sn, const Geom& G, const Work<T>& W, int stage,
+                                        double gamma, double eta_d, int strips, int q) {
+  int t = q;
+  if (few_flagged(G, W.nflag[stage])) {
+    const int f = flag_list(W)[q / 27], k = q % 27;
+    t = interior_id(G, f % G.n[0] + k % 3 - 1 + G.g, f / G.n[0] % G.n[1] + k / 3 % 3 - 1 + G.g,
+                    f / (G.n[0] * G.n[1]) + k / 9 - 1 + G.g);
+  }
+  unsigned* w = item_word(W, t / (kBlock * strips));
+  w[0] = w[1] = 0;
+  fo_at<T, EMF>(Sn, G, W, stage, gamma, eta_d, t, false);
+}
+
 template <typename T, int EMF>
 __global__ void __launch_bounds__(kBlock)
     k_fo(State Sn, Geom G, Work<T> W, int stage, double gamma, double eta_d, const int* stop) {
@@ -1702,9 +1816,9 @@ __global__ void __launch_bounds__(kBlock)
   if (W.nflag[stage] == 0) return;
   // grid-stride: the launch is capped, so that the usual case (nothing
   // flagged) costs a few workgroups, not one per 256 cells
-  const int ninter = G.n[0] * G.n[1] * G.n[2];
-  for (int t = gidx(); t < ninter; t += (int)gridDim.x * kBlock)
-    fo_at<T, EMF>(Sn, G, W, stage, gamma, eta_d, t, false);
+  const int n = fo_units(G, W, stage);
+  for (int q = gidx(); q < n; q += (int)gridDim.x * kBlock)
+    fo_unit<T, EMF>(Sn, G, W, stage, gamma, eta_d, 1, q);
 }
 
 // ---------------------------------------------------------------------------
@@ -2003,9 +2117,14 @@ __device__ __forceinline__ void batch_item(const BatchArgs<T>& A, int b, int sta
     else
       update_item<T, 1, fix>(cur, Hs, oth, G, W, U, A.diag, tile, strips, W.smax, fix);
   } else if constexpr (KIND == PH_O) {
-    for (int s = 0; s < strips; ++s)
-      fo_at<T, EMF>(cur, G, W, stage, A.gamma, A.eta, (tile * strips + s) * kBlock + threadIdx.x,
-                    A.level != 0);
+    const int n = A.level ? 0 : fo_units(G, W, stage);
+    for (int s = 0; s < strips; ++s) {
+      const int q = (tile * strips + s) * kBlock + threadIdx.x;
+      if (A.level)
+        fo_at<T, EMF>(cur, G, W, stage, A.gamma, A.eta, q, true);
+      else if (q < n)
+        fo_unit<T, EMF>(cur, G, W, stage, A.gamma, A.eta, strips, q);
+    }
   } else if constexpr (KIND == PH_WRAP) {
     double sig = 0.0;
     for (int s = 0; s < strips; ++s) {
