@@ -93,7 +93,7 @@ long long item_count(int kind, const Geom& G, const FacePlan& FP, long long per,
 
 // Layout and meaning of a plan's contents: part of its key, so that a plan
 // kept from a library with another one is refused.
-constexpr int kPlanVersion = 2;
+constexpr int kPlanVersion = 3;
 
 // FNV-1a over everything a plan depends on: the kernel refuses a plan whose
 // key differs from the one computed for the call's own parameters and boxes.

@@ -250,17 +250,18 @@ DtStep make_dt_step(const ctmhd_params* p, const Work<T>& W, int npart, int n,
 // faces of the two marching directions of all boxes of a call: chunks of 32
 // faces once they make kFaceWaves wavefronts, shorter ones on smaller calls,
 // down to one face.  A call of many boxes, whose marches are of uneven length,
-// takes at most 16, or 64 once it fills the chip many times over.  A chunk is a
-// serial chain of one Riemann solve (about 2 us) per face and 2r + 1 cheaper
-// cells to fill its pipeline.  Measured per step, FP64 PPM: 16^3 94 us with
-// chunks of 1, 112 with 4, 183 with 32; 64^3 267 / 220 / 216 / 241 / 329 us with
-// 1 / 4 / 8 / 16 / 32; 128^3 1259 / 1194 / 1165 / 1155 us with 4 / 8 / 16 / 32; 100
-// uneven boxes 2.21 / 2.38 / 2.73 ms with 16 / 32 / 64, 2000 of them 37.4 / 37.4 /
-// 36.7 ms (FP32 30.4 / 30.6 / 27.7).
+// takes at most 16.  A chunk is a serial chain of one Riemann solve (about 2 us)
+// per face and 2r + 1 cheaper cells to fill its pipeline.  Measured per step,
+// FP64 PPM: 16^3 94 us with chunks of 1, 112 with 4, 183 with 32; 64^3 267 / 220 /
+// 216 / 241 / 329 us with 1 / 4 / 8 / 16 / 32; 128^3 1259 / 1194 / 1165 / 1155 us
+// with 4 / 8 / 16 / 32; uneven boxes with 4 / 8 / 16 / 64: 2000 in FP32 29.6 / 29.7 /
+// 30.1 / 31.2 ms, in FP64 39.1 / 38.1 / 37.6 / 37.5, 500 in FP32 7.18 / 7.30 / 7.40 /
+// 7.88, in FP64 9.76 / 9.69 / 9.68 / 10.17 (the plan, which holds the chunk,
+// serves every precision).
 constexpr int kFaceWaves = 1024;
 int auto_face_chunk(long long faces, int nbox) {
   const long long c = faces / (64LL * kFaceWaves);
-  const long long most = nbox == 1 ? 32 : (c >= 512 ? 64 : 16);
+  const long long most = nbox == 1 ? 32 : 16;
   return c < 1 ? 1 : (c > most ? (int)most : (int)c);
 }
 // Items per wavefront of the x part, one to four: 16^3 108 us with 4 against
