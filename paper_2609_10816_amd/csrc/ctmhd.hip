@@ -6,8 +6,8 @@
 //                of steps, the copy into the other buffer
 //   per stage:
 //   k_faces      reconstruction + Riemann solve at every face of all three
-//                directions in one launch: x faces inside a wavefront (cross-
-//                lane shuffles), y and z faces by marching along the face
+//                directions in one launch: x faces inside a wavefront (whole-
+//                wavefront shifts), y and z faces by marching along the face
 //                normal with a register window, so that every cell is loaded
 //                and reconstructed once per direction; primitives are formed
 //                on the fly (pressure recovery in FP64); in the first stage an
@@ -15,14 +15,17 @@
 //                starting state (or takes the caller's); a non-finite dt stops
 //                the call
 //   k_emf_march  Q26 edge EMFs of the three edge directions with LD04
-//                averaging and eta j, one thread per column of edges marching
-//                up z (the z reconstructions streamed through registers)
-//   k_emf3       the same for B25a / FS18, one thread per edge position
+//                averaging and eta j, a row of edge columns per wavefront
+//                marching up z (z reconstructions streamed through registers,
+//                x ones across the wavefront)
+//   k_emf3       the same for small boxes and for B25a / FS18, one thread per
+//                edge position (and direction, on the smallest)
 //   k_update     flux divergence and CT curl, RK combination, periodic ghost
 //                images, invalid-state flags and (second stage) the CFL
 //                maximum of the new state for the next step
 //   k_fo         first-order fluxes / EMFs from S^n around flagged cells
-//   k_update     again (fix-up mode), only when something was flagged
+//   k_update     again (fix-up mode), only when something was flagged, for the
+//                cells those values reach
 // Face arrays hold the x_a face on the lower side of each cell, edge arrays
 // the edge at the lower corner in the two transverse directions.
 #include "ctmhd_host.h"
