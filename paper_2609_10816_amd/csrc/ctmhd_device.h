@@ -1937,9 +1937,14 @@ template <typename T>
 __device__ __forceinline__ Work<T> shift_work(const BatchArgs<T>& A, long long off, int elems) {
   const Work<T>& W0 = A.W;
   Work<T> W = W0;
+  // k from the quotient in double, exact after rounding (p is k strides from the
+  // base, k in the tens).  With a 64-bit integer division for each of the
+  // sixty-odd pointers the table took 26 us for 64 boxes and 35 us for 2000, so 13
+  // and 24.
+  const double per = 1.0 / (double)A.wstride;
   auto box = [&](T* p) -> T* {
     if (!p) return nullptr;
-    const long long k = (p - A.wbase) / A.wstride;
+    const long long k = (long long)(int)((double)(p - A.wbase) * per + 0.5);
     return A.wbase + off * A.narr + k * elems;
   };
 #pragma unroll
