@@ -11,6 +11,7 @@
 
 #include "ctmhd.h"
 #include "ctmhd_math.h"
+#include "ctmhd_workgroup.h"
 
 using namespace ctmhd;
 
@@ -107,7 +108,6 @@ struct State {
   double* b[3];
 };
 
-constexpr int kBlock = 256;
 constexpr int kMaxSlots = 64;  // spread of the CFL maximum over atomics
 
 template <typename T>
@@ -231,27 +231,8 @@ __device__ __forceinline__ double cfl_signal(double rho, const double u[3], doub
   return s;
 }
 
-// Block maximum of a non-negative (or NaN) double, as its bit pattern (a NaN
-// has larger bits than +inf as an unsigned integer); valid in thread 0.  All
-// threads must call.
-__device__ __forceinline__ unsigned long long block_max_bits(double s) {
-  __shared__ unsigned long long red[kBlock / 64];
-  unsigned long long bits = (unsigned long long)__double_as_longlong(s);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    unsigned long long ob = __shfl_xor(bits, o, 64);
-    bits = ob > bits ? ob : bits;
-  }
-  int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
-  if (lane == 0) red[w] = bits;
-  __syncthreads();
-  unsigned long long m = 0;
-  if (threadIdx.x == 0)
-    for (int q = 0; q < (int)(blockDim.x >> 6); ++q) m = red[q] > m ? red[q] : m;
-  return m;
-}
-
-// The same folded into one of kMaxSlots device slots by an atomic max.
+// The maximum of a workgroup (block_max_bits) folded into one of kMaxSlots
+// device slots by an atomic max.
 __device__ __forceinline__ void block_max_to_slots(double s, unsigned long long* slots, int slot) {
   const unsigned long long m = block_max_bits(s);
   if (threadIdx.x == 0) atomicMax(&slots[slot], m);
