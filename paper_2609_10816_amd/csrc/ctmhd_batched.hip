@@ -93,7 +93,7 @@ long long item_count(int kind, const Geom& G, const FacePlan& FP, long long per,
 
 // Layout and meaning of a plan's contents: part of its key, so that a plan
 // kept from a library with another one is refused.
-constexpr int kPlanVersion = 3;
+constexpr int kPlanVersion = 4;
 
 // FNV-1a over everything a plan depends on: the kernel refuses a plan whose
 // key differs from the one computed for the call's own parameters and boxes.
@@ -624,8 +624,6 @@ int build_plan(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, const Le
     d.off = bx.offset;
     d.flag_off = L ? bx.offset : flag_off;  // a level indexes flags by storage position
     flag_off += box_inter_ll(bx);
-    double dxmin = fmin(bx.dx[0], fmin(bx.dx[1], bx.dx[2]));
-    d.sres = p->eta > 0.0 ? 2.0 * p->eta / (dxmin * dxmin) : 0.0;
   }
   long long items_in_launch = 0;
   int launch = 0;

@@ -1837,7 +1837,6 @@ struct BoxDesc {
   FacePlan FP;
   long long off;       // element offset of the box in the packed field arrays
   long long flag_off;  // offset of the box in the packed flag array
-  double sres;         // resistive term of the CFL maximum (depends on dx)
 };
 
 struct PlanHeader {
@@ -1896,7 +1895,7 @@ struct BoxTab {
   Work<T> w;         // its stencil arrays and per-box scalars
   Geom G;
   FacePlan FP;
-  double sres;
+  double sres;  // resistive term of the CFL maximum
 };
 
 __device__ __forceinline__ State shift_state(const State& S, long long off) {
@@ -2160,7 +2159,9 @@ __global__ void __launch_bounds__(kBlock) k_btab(BatchArgs<T> A, int nbox) {
   tb->w = W;
   tb->G = d.G;
   tb->FP = d.FP;
-  tb->sres = d.sres;
+  // from the call's eta: one plan serves calls of any eta
+  const double dxmin = fmin(d.G.dx[0], fmin(d.G.dx[1], d.G.dx[2]));
+  tb->sres = A.eta > 0.0 ? 2.0 * A.eta / (dxmin * dxmin) : 0.0;
 }
 
 // Flag counters of box b.
