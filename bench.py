@@ -183,7 +183,7 @@ def run_batched_form(K, W, log_tune=True):
         if precision == "fp32":
             tile, tms = autotune.tune_batched(P, st, steps=2, reps=1)
             log("autotune (ms/step): " + ", ".join(
-                f"{'persistent' if int(k) >> 16 else 'per-phase'} chunk {int(k) & 255}"
+                f"{'persistent' if int(k) >> 16 else 'per-phase'} chunk {int(k) & 255 or 'auto'}"
                 f"/strips {(int(k) >> 8) & 255}: {v:.2f}" for k, v in tms.items()))
         P.tile = tile
         S = ctmhd.BatchedStepper(P, st)
@@ -212,10 +212,10 @@ def run_batched_form(K, W, log_tune=True):
                           "fofc_flagged_cells": int(dg[:, :2].sum()),
                           "queue_wait_timeout": bool((dg[:, 3] & 2).any())}
         if precision == "fp32":
-            out["tile"] = {"chunk": tile & 255 or 32, "strips": ((tile >> 8) & 255) or 1,
+            out["tile"] = {"chunk": tile & 255 or "auto", "strips": ((tile >> 8) & 255) or 1,
                            "schedule": "persistent" if tile >> 16 else "per-phase"}
             out["autotune_ms_per_step"] = {
-                f"{'persistent' if int(k) >> 16 else 'per-phase'}/chunk{int(k) & 255}"
+                f"{'persistent' if int(k) >> 16 else 'per-phase'}/chunk{int(k) & 255 or 'auto'}"
                 f"/strips{(int(k) >> 8) & 255}": v for k, v in tms.items()}
             # the same boxes, one ctmhd_step call per box and step
             ws = torch.empty(max(ctmhd.workspace_bytes(P, ctmhd.make_box(b.n, b.ng, b.dx))

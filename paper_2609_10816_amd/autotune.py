@@ -5,7 +5,9 @@ The library exposes two tuning knobs through ``ctmhd_params.tile``:
 * ``chunk``  - minimum number of faces one workgroup marches along the y and
   z normals before a new march starts (shorter chunks give more workgroups
   and more warm-up reconstructions; longer chunks give fewer, longer
-  workgroups);
+  workgroups); 0 lets the library choose from the size of the call, and is
+  always among the settings tried, so that a tuned call is no slower than an
+  untuned one;
 * ``strips`` - 256-cell strips per work item of the batched call (more
   strips give fewer, longer work items);
 * ``schedule`` - the batched call launches once per phase over all boxes
@@ -18,25 +20,32 @@ batched search is coordinate-wise: per schedule, the chunk at the default
 strips, then the strips at the best chunk.  The tuner times whole
 steps on a copy of the caller's state, on the stream the library launches on,
 and returns the fastest knob value; results are cached per
-(scheme, precision, box-shape signature) for the life of the process and,
-optionally, in a JSON file.
+(scheme, precision, box-shape signature, build of the library) for the life of
+the process and, optionally, in a JSON file.
 """
 from __future__ import annotations
 
+import functools
 import hashlib
 import json
 import os
 
 from . import ctmhd
 
-CHUNKS = (8, 16, 32, 64)
+CHUNKS = (0, 8, 16, 32, 64)
 STRIPS = (1, 2, 4, 8)
 
 _cache: dict[str, dict] = {}
 
 
+@functools.lru_cache(maxsize=None)
+def _library_tag(path) -> str:
+    with open(path, "rb") as f:
+        return hashlib.sha1(f.read()).hexdigest()
+
+
 def _signature(params: ctmhd.Params, shapes) -> str:
-    h = hashlib.sha1()
+    h = hashlib.sha1(_library_tag(ctmhd.LIB_PATH).encode())
     h.update(repr((params.recon, params.riemann, params.emf_compute, params.fofc,
                    params.precision, params.eta > 0)).encode())
     for n in shapes:
