@@ -71,7 +71,8 @@ def log(msg):
 
 
 # the files the face kernel is compiled from
-FACE_KERNEL_SOURCES = ("ctmhd.hip", "ctmhd_device.h", "ctmhd_host.h", "ctmhd_math.h")
+FACE_KERNEL_SOURCES = ("ctmhd.hip", "ctmhd_device.h", "ctmhd_host.h", "ctmhd_math.h",
+                       "ctmhd_workgroup.h")
 
 
 def kernel_source_hash():

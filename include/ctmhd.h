@@ -90,7 +90,7 @@ typedef struct ctmhd_params {
   int32_t precision;     /* CTMHD_FP64, CTMHD_FP32 or CTMHD_FP32_R64 */
   int32_t tile;          /* launch-shape knob (0 = defaults): bits 0-7 minimum faces per
                             marching chunk of the face pass (0: by the size of the
-                            call, up to 32), bits 8-15
+                            call, up to 32, of several boxes up to 16), bits 8-15
                             256-element strips per work item of the batched call (default 1),
                             bit 16 schedule of the batched call (0 one launch per phase,
                             1 one persistent launch per step), bits 19-20 XCD mapping of
@@ -148,8 +148,9 @@ int ctmhd_step(const ctmhd_params* p, const ctmhd_box* box, double* const cons[5
 /* Batched boxes (the AMR-like form): plan of the work queue.  The plan is
  * built on the host into a caller buffer of ctmhd_batch_plan_bytes() bytes
  * (boxes: HOST array) and must be copied by the caller into device memory
- * before ctmhd_step_batched; it depends on params (scheme, tile knob, fofc)
- * and on the boxes only, so one upload serves every later call. */
+ * before ctmhd_step_batched; it depends on params (recon, emf_compute, fofc,
+ * tile knob) and on the boxes only, so one upload serves every later call,
+ * also of another gamma, eta, cfl, Riemann solver or precision. */
 size_t ctmhd_batch_plan_bytes(const ctmhd_params* p, const ctmhd_box* boxes, int nbox);
 int ctmhd_batch_plan(const ctmhd_params* p, const ctmhd_box* boxes, int nbox, void* host_plan,
                      size_t bytes);

@@ -673,8 +673,8 @@ __device__ __forceinline__ float lane_next(float v) {
 // x faces: one wavefront holds 64 consecutive cells of a row; lane l forms
 // the primitives, the limited slope and the upper interface value of its own
 // cell, neighbours come from whole-wavefront DPP shifts by one lane, and the
-// face at lane l takes the upper value of lane l-1.  Faces at lanes [r+1, 63-r] are resolved
-// (overlapping segments).
+// face at lane l takes the upper value of lane l-1.  Faces at lanes [r+1, 63-r]
+// are resolved; the next 64 cells start 2r + 1 before the end of these.
 template <int RECON, typename T>
 __device__ __forceinline__ void recon_lanes(T q, T& qm, T& qp) {
   if constexpr (RECON == kPC) {
@@ -1402,9 +1402,12 @@ struct UpdateCfg {
 };
 
 // The new conserved values c and lower face fields bl of the cell at s and,
-// with need_state, its upper face fields bu, recomputed with the same arithmetic
-// as the neighbour that owns them (for the flags and the CFL signal).  fix: the
-// form after a first-order replacement.
+// with need_state, its upper face fields bu (for the flags and the CFL signal).
+// fix: the form after a first-order replacement.  bu takes the form of this
+// cell, which is the one its owner stored but at the rim of a fix-up: between a
+// rewritten cell and an unwritten one the two forms of the second stage differ
+// by round-off, and so does the CFL signal there from that of the stored state.
+// The stored fields have one owner each and are single-valued.
 template <typename T, int stage, int fix>
 __device__ __forceinline__ void cell_form(const State& base, const State& half, const Geom& G,
                                           const Work<T>& W, bool need_state, int s, double dt,
@@ -2239,6 +2242,12 @@ __global__ void __launch_bounds__(kBlock) k_batch(BatchArgs<T> A) {
   }
 }
 
+// Consecutive items per XCD (k_bphase).  Step with bands of 8 / 64 / 256 items
+// and without: 2000 uneven boxes, FP32 31.2 / 30.1 / 29.8 / 31.5 ms, FP64 38.6 /
+// 37.8 / 37.4 / 40.0; 300 boxes, FP64 5.48 / 5.37 / 5.39 / 5.50; a level of 64
+// boxes of 32^3 1.91 / 1.89 / 1.90 / 1.94 ms.  Below about 60 boxes a few bands
+// hold all items and share the XCDs out unevenly: 40 boxes, FP64, 0.78 / 0.84 /
+// 0.78 / 0.79 ms.
 constexpr int kBatchBand = 64;
 
 // The lookup of an item's box reads the plan as constant memory (nothing writes

@@ -283,9 +283,12 @@ long long march_faces(const ctmhd_box& b, int recon, int emf, bool periodic) {
 // from the 256 MB Infinity Cache after the first.  Measured per launch, without
 // and with: FP32 PPM 160^3 (0.3 GB) 396 / 404 us, 200^3 814 / 742, 256^3 1601 /
 // 1354, 384^3 5264 / 4670; FP64 PLM 256^3 1947 / 1755; FP64 PC 384^3 6143 /
-// 5580.  FP64 PPM with HLLD is held up by its arithmetic instead (256^3 2088 /
-// 2082, 512^3 16.40 / 16.50 ms), and keeps one brick, whose long marches all
-// start first.
+// 5580; FP64 PPM LLF 200^3 989 / 826, 256^3 1925 / 1528; FP32 with the FP64
+// Riemann solve, HLLD, PLM 200^3 774 / 718, 256^3 1551 / 1389, PPM 200^3 826 /
+// 845, 256^3 1656 / 1619, 320^3 3217 / 3052 (the step: 2562 / 2601 at 184^3, 4063
+// / 4066 at 216^3, 4922 / 4822 at 232^3).  FP64 PPM with HLLD is held up by its
+// arithmetic instead (256^3 2088 / 2082, 512^3 16.40 / 16.50 ms), and keeps one
+// brick, whose long marches all start first.
 constexpr long long kBrickFrom = 384LL << 20, kBrickBytes = 64LL << 20;
 // Face plan: ranges and launch shape of the fused face kernel.  What the tile
 // knob leaves open is chosen from `faces`, march_faces summed over the nbox
@@ -401,7 +404,12 @@ int launch_faces(hipStream_t st, const ctmhd_params* p, State S, const Geom& G, 
 // short) and the shortest z chunk
 constexpr int kEmfTiles = 32768;
 constexpr int kEmfMinChunk = 5;
-// Workgroups of the per-edge kernel up to which it is split by direction
+// Workgroups of the per-edge kernel up to which it is split by direction: two
+// per CU, from where on three edges per thread fill the chip as well.  Step
+// without / with the split, FP64, us: PPM Q26 16^3 76 / 64, 32^3 81 / 71, 48^3
+// (460 workgroups) 121 / 116, 56^3 (724) 153 / 152, 80^3 (2076) 323 / 329; PPM FS18
+// 32^3 118 / 104, 48^3 169 / 169, 56^3 213 / 218, 64^3 (1073) 294 / 282, 80^3 497 /
+// 504; PLM Q26 32^3 66 / 65, 48^3 94 / 96, 56^3 123 / 126.
 constexpr int kEmfSplitBlocks = 512;
 
 // Workgroups of the z-marching edge kernel that the device holds at once (0 if
